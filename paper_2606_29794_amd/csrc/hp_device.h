@@ -54,6 +54,7 @@ HP_HD HpGridView hp_grid_view(void* base, const HpGeom& g) {
 struct HpMaskView {
   int64_t* n_active;
   int32_t* n_tiles;
+  float* cone;            // (sin, cos) of half the bounding cone's angle (hp_cone.h)
   int32_t* tile_start;    // [ntile] first compact pixel slot of the tile
   int32_t* tile_count;    // [ntile] active pixels in the tile
   int32_t* tile_compact;  // [ntile] compact active tile id or -1
@@ -76,6 +77,7 @@ HP_HD HpMaskView hp_mask_view(P* base, const HpGeom& g) {
   char* p = (char*)base;
   v.n_active = (int64_t*)p;
   v.n_tiles = (int32_t*)(p + 8);
+  v.cone = (float*)(p + 16);
   p += 256;
   size_t t4 = hp_align256(g.ntile * 4);
   v.tile_start = (int32_t*)p; p += t4;

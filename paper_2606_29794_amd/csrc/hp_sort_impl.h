@@ -219,9 +219,8 @@ inline hp_status scan_exclusive(const In* in, T* out, const uint64_t* cnt, int64
 // within that digit)
 __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                          const uint64_t* __restrict__ cnt, int64_t cap, int shift,
-                                                         int bits, uint32_t* __restrict__ hist, int64_t* mark) {
+                                                         int bits, uint32_t* __restrict__ hist) {
   __shared__ uint32_t s_h[256];
-  if (mark && blockIdx.x == 0 && threadIdx.x == 0) *mark = INT64_MAX;
   const int radix = 1 << bits;
   const uint32_t mask = (uint32_t)radix - 1;
   for (int d = threadIdx.x; d < radix; d += kThreads) s_h[d] = 0;
@@ -266,13 +265,17 @@ __global__ __launch_bounds__(kThreads) void k_radix_digit_scan(uint32_t* __restr
 // running count per digit, private to the wave, carries the rank across
 // rounds.  The tile is then placed in LDS sorted by digit, so that the global
 // writes go out as contiguous runs per digit, and the block's running digit
-// offsets advance by the tile's digit counts.
+// offsets advance by the tile's digit counts.  FIRST (see RadixFirst): each
+// key's value is its index, keys of `limit` and above are dropped (their
+// histogram left them out), and the first block stores how many remain.
+template <bool FIRST>
 __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __restrict__ keys,
                                                             const uint32_t* __restrict__ vals,
                                                             const uint64_t* __restrict__ cnt, int64_t cap, int shift,
-                                                            int bits, const uint32_t* __restrict__ offs,
+                                                            int bits, uint32_t limit, const uint32_t* __restrict__ offs,
                                                             const uint32_t* __restrict__ dtot,
-                                                            uint32_t* __restrict__ okeys, uint32_t* __restrict__ ovals) {
+                                                            uint32_t* __restrict__ okeys, uint32_t* __restrict__ ovals,
+                                                            uint64_t* kept) {
   constexpr int kWaveItems = kRadixTile / 4;  // 256
   constexpr int kRounds = kWaveItems / 64;     // 4
   __shared__ uint32_t s_cnt[4][256];
@@ -294,6 +297,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __re
     uint32_t all;
     const uint32_t dpre = block_exclusive<uint32_t>(tid < radix ? dtot[tid] : 0u, &all, s_wsum);
     if (tid < radix) s_goff[tid] = dpre + offs[(int64_t)tid * gridDim.x + blockIdx.x];
+    if (FIRST && blockIdx.x == 0 && tid == 0) *kept = all;
   }
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   for (int64_t t = t0; t < t1; ++t) {
@@ -301,13 +305,15 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __re
     __syncthreads();
     const int64_t base = t * kRadixTile;
     uint32_t rk[kRounds], kk[kRounds], vv[kRounds];
+    bool in[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
       const int64_t i = base + (int64_t)w * kWaveItems + r * 64 + lane;
-      const bool valid = i < n;
-      const uint32_t key = valid ? keys[i] : 0u;
+      const uint32_t key = i < n ? keys[i] : 0u;
+      const bool valid = i < n && (!FIRST || key < limit);
+      in[r] = valid;
       kk[r] = key;
-      vv[r] = valid ? (vals ? vals[i] : (uint32_t)i) : 0u;  // no values: each key's index
+      vv[r] = FIRST ? (uint32_t)i : (valid ? vals[i] : 0u);
       const uint32_t d = (key >> shift) & mask;
       uint64_t peers = __ballot(valid);
       for (int b = 0; b < bits; ++b) {
@@ -338,8 +344,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __re
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-      const int64_t i = base + (int64_t)w * kWaveItems + r * 64 + lane;
-      if (i < n) {
+      if (in[r]) {
         const uint32_t d = (kk[r] >> shift) & mask;
         const uint32_t lp = s_loc[d] + s_cnt[w][d] + rk[r];
         s_key[lp] = kk[r];
@@ -347,8 +352,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __re
       }
     }
     __syncthreads();
-    const int nloc = (int)(n - base < kRadixTile ? n - base : kRadixTile);
-    for (int lp = tid; lp < nloc; lp += kThreads) {
+    for (int lp = tid; lp < (int)all; lp += kThreads) {
       const uint32_t key = s_key[lp];
       const uint32_t d = (key >> shift) & mask;
       const uint32_t g = s_goff[d] + ((uint32_t)lp - s_loc[d]);
@@ -358,17 +362,6 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(const uint32_t* __re
     __syncthreads();
     // the tile's digit counts move the block's offsets on
     if (tid < radix) s_goff[tid] += tot;
-  }
-}
-
-// keys[i] = src[i], vals[i] = i
-__global__ void k_keys_iota(const uint32_t* __restrict__ src, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                            const uint64_t* __restrict__ cnt, int64_t cap, int64_t* mark) {
-  if (mark && blockIdx.x == 0 && threadIdx.x == 0) *mark = INT64_MAX;
-  const int64_t n = dev_count(cnt, cap);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    keys[i] = src[i];
-    vals[i] = (uint32_t)i;
   }
 }
 
@@ -389,51 +382,64 @@ inline size_t radix_ws_bytes(int64_t cap) {
   return 2 * hp_align256((size_t)(cap > 0 ? cap : 1) * 4) + hp_align256((size_t)h * 4) + hp_align256(256 * 4);
 }
 
+// A sort whose first histogram the caller has made (with radix_grid(cap)
+// blocks over block_tiles, 8 bits from bit 0, digit-major): `keys` are read
+// by the first pass with their indices as values, those of `limit` and above
+// are dropped, and *kept receives the number that remain.
+struct RadixFirst {
+  const uint32_t* keys;
+  uint32_t limit;
+  uint64_t* kept;
+};
+
+// where the caller of a RadixFirst sort writes its histogram
+inline uint32_t* radix_hist_ptr(void* ws, int64_t cap) {
+  return (uint32_t*)((char*)ws + 2 * hp_align256((size_t)(cap > 0 ? cap : 1) * 4));
+}
+
 // Stable sort of the first min(*cnt, cap) (key, value) pairs by the low
 // `nbits` bits of the key (cnt null: cap pairs).  The result is left in
 // (keys, vals), or, when out_keys / out_vals are given, in whichever of
 // (keys, vals) and the workspace's second buffer the last pass wrote
-// (returned through them; no copy back).  With first_keys, the input keys are
-// read from there and each element's value is its index: keys and vals are
-// then outputs only.  With mark (device, nullable), the sort's first kernel
-// also sets *mark = INT64_MAX (a caller's "not yet counted" flag, set by the
-// first kernel of its sequence); first_keys is required then.
+// (returned through them; no copy back).  With first (then cnt null and 32
+// bits), the input comes from there; keys and vals are then outputs only
+// (first->keys may be the keys buffer: the first pass writes the other one).
 inline hp_status radix_sort(uint32_t* keys, uint32_t* vals, const uint64_t* cnt, int64_t cap, int nbits, void* ws,
                             hipStream_t s, uint32_t** out_keys = nullptr, uint32_t** out_vals = nullptr,
-                            const uint32_t* first_keys = nullptr, int64_t* mark = nullptr) {
+                            const RadixFirst* first = nullptr) {
   if (out_keys) *out_keys = keys;
   if (out_vals) *out_vals = vals;
-  if (mark && (!first_keys || cap <= 0)) return HP_ERR_INVALID_ARG;
+  if (first && (cnt || nbits != 32)) return HP_ERR_INVALID_ARG;
   if (cap <= 0) return HP_OK;
-  if (cap == 1 || nbits <= 0) {
-    if (first_keys) {
-      hipLaunchKernelGGL(k_keys_iota, dim3(copy_grid(cap)), dim3(256), 0, s, first_keys, keys, vals, cnt, cap, mark);
-      HP_CHECK_LAUNCH();
-    }
-    return HP_OK;
-  }
+  if (!first && (cap == 1 || nbits <= 0)) return HP_OK;
   const int passes = (nbits + 7) / 8;
   const int bits = (nbits + passes - 1) / passes;
   const unsigned G = radix_grid(cap);
   char* p = (char*)ws;
   uint32_t* k2 = (uint32_t*)p; p += hp_align256((size_t)cap * 4);
   uint32_t* v2 = (uint32_t*)p; p += hp_align256((size_t)cap * 4);
-  uint32_t* hist = (uint32_t*)p; p += hp_align256((size_t)G * 256 * 4);
+  uint32_t* hist = radix_hist_ptr(ws, cap); p += hp_align256((size_t)G * 256 * 4);
   uint32_t* dtot = (uint32_t*)p;
   uint32_t *ka = keys, *va = vals, *kb = k2, *vb = v2;
   for (int pass = 0; pass < passes; ++pass) {
     const int shift = pass * bits;
     const int b = (shift + bits <= nbits) ? bits : nbits - shift;
-    const uint32_t* src_k = (pass == 0 && first_keys) ? first_keys : ka;
-    const uint32_t* src_v = (pass == 0 && first_keys) ? nullptr : va;
-    hipLaunchKernelGGL(k_radix_hist, dim3(G), dim3(kThreads), 0, s, src_k, cnt, cap, shift, b, hist,
-                       pass == 0 ? mark : nullptr);
-    HP_CHECK_LAUNCH();
+    const bool f = pass == 0 && first;
+    const uint32_t* src_k = f ? first->keys : ka;
+    if (!f) {
+      hipLaunchKernelGGL(k_radix_hist, dim3(G), dim3(kThreads), 0, s, src_k, cnt, cap, shift, b, hist);
+      HP_CHECK_LAUNCH();
+    }
     hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << b), dim3(kThreads), 0, s, hist, (int)G, dtot);
     HP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_radix_scatter, dim3(G), dim3(kThreads), 0, s, src_k, src_v, cnt, cap, shift, b,
-                       (const uint32_t*)hist, (const uint32_t*)dtot, kb, vb);
+    if (f)
+      hipLaunchKernelGGL(k_radix_scatter<true>, dim3(G), dim3(kThreads), 0, s, src_k, (const uint32_t*)nullptr, cnt, cap,
+                         shift, b, first->limit, (const uint32_t*)hist, (const uint32_t*)dtot, kb, vb, first->kept);
+    else
+      hipLaunchKernelGGL(k_radix_scatter<false>, dim3(G), dim3(kThreads), 0, s, src_k, (const uint32_t*)va, cnt, cap,
+                         shift, b, 0u, (const uint32_t*)hist, (const uint32_t*)dtot, kb, vb, (uint64_t*)nullptr);
     HP_CHECK_LAUNCH();
+    if (f) cnt = first->kept;  // the later passes see the kept keys alone
     uint32_t* t = ka; ka = kb; kb = t;
     t = va; va = vb; vb = t;
   }

@@ -1,6 +1,7 @@
 // k_grid_mask.hip -- HEALPix grid tables (tile and quadtree caps) and the
 // camera visibility mask M_C of Sec. 3.1.
 #include "hp_common.h"
+#include "hp_cone.h"
 
 // ---------------------------------------------------------------------------
 // Grid: leaf caps (one block per tile, one thread per pixel)
@@ -149,10 +150,10 @@ __global__ __launch_bounds__(256) void k_mask_tiles(int order, int b, int cam, d
 }
 
 // single block: exclusive scans of tile counts (pixel slots) and of the
-// active-tile flags (compact ids); totals to the header
+// active-tile flags (compact ids); totals and the bounding cone to the header
 __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t* count, int32_t* start,
                                                     int32_t* compact, int32_t* active_tiles, int64_t* n_active,
-                                                    int32_t* n_tiles) {
+                                                    int32_t* n_tiles, HpCone cone_val, float* cone) {
   __shared__ int64_t s_pix[1024];
   __shared__ int32_t s_til[1024];
   const int tid = threadIdx.x;
@@ -177,7 +178,12 @@ __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t
     else compact[i] = -1;
     bp += count[i];
   }
-  if (tid == 1023) { *n_active = s_pix[1023]; *n_tiles = s_til[1023]; }
+  if (tid == 1023) {
+    *n_active = s_pix[1023];
+    *n_tiles = s_til[1023];
+    cone[0] = cone_val.sr;
+    cone[1] = cone_val.cr;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_mask_pix(int b, const uint32_t* bits, const int32_t* start, int32_t* out) {
@@ -222,7 +228,7 @@ extern "C" hp_status hp_mask(const hp_view* view, const hp_params* prm, const vo
                      (double)view->fov_x, (double)view->fov_y, m.tile_bits, m.tile_count);
   HP_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_mask_scan, dim3(1), dim3(1024), 0, s, g.ntile, m.tile_count, m.tile_start, m.tile_compact,
-                     m.active_tiles, m.n_active, m.n_tiles);
+                     m.active_tiles, m.n_active, m.n_tiles, hp_view_cone(view, g.kt), m.cone);
   HP_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_mask_pix, dim3((unsigned)g.ntile), dim3(256), 0, s, g.b, m.tile_bits, m.tile_start, m.active_pix);
   HP_CHECK_LAUNCH();
