@@ -33,6 +33,7 @@ struct BinWs {
   uint64_t* ncol;     // (chunk, leaf) count entries to scan (sorted emission)
   uint32_t* over;     // 1 when the tasks exceeded cap_t
   uint64_t* n_live;   // Gaussians in depth order (those that can reach an active tile)
+  uint64_t* n_over;   // tasks in the walk's overflow part (zeroed by the depth sort's first kernel)
   void* sort_ws;
   void* scan_ws;
   int64_t cap_t;
@@ -65,6 +66,7 @@ static BinWs bin_ws(void* base, int64_t P) {
   w.ncol = (uint64_t*)(p + 24);
   w.over = (uint32_t*)(p + 32);
   w.n_live = (uint64_t*)(p + 40);
+  w.n_over = (uint64_t*)(p + 48);
   p += 256;
   w.sort_ws = p; p += hpsort::radix_ws_bytes(P);
   w.scan_ws = p;
@@ -333,78 +335,346 @@ __global__ __launch_bounds__(256) void k_bin_coarse(int64_t P, const uint64_t* _
 }
 
 // ---- task list in node order without a sort --------------------------------
-// For split levels of at most kHistNodes nodes.  The count walk also counts
-// each workgroup's tasks per node into a node-major histogram [nn][G] (G
-// workgroups of 256 Gaussians in depth order).  An exclusive scan of the
-// histogram (each node's row scanned by its own workgroup, then the node
-// offsets added) gives every (node, workgroup) its first slot, and the scatter
-// pass writes each task straight to its place: that slot plus the number of
-// the workgroup's earlier Gaussians with a task at the node.  A Gaussian has
-// at most one task per node, so this is the order a stable sort of the
-// depth-ordered tasks by node gives.
-constexpr int kHistNodes = 768;
-static_assert(kHistNodes <= 4 * 256, "k_task_segments takes four nodes per thread");
+// For split levels of at most kListNodes nodes.  A workgroup walks the tree for
+// 256 Gaussians (in depth order) over one group of kWalkGroup split-level
+// nodes, and leaves their tasks in node order, depth order inside a node, in
+// a run of its own, with its task count per node in a node-major histogram
+// [nn][G] (G workgroups of Gaussians).  An exclusive scan of every histogram
+// row and of the node totals then gives each (node, workgroup) its first
+// slot, and k_task_place moves the runs there: the order that a stable sort
+// of the depth-ordered tasks by node gives.
+constexpr int kWalkGroup = 768;
+constexpr int kListNodes = 4 * kWalkGroup;
+constexpr int kStageFixed = 4096;  // staged tasks per 256 Gaussians; the rest overflow
+static_assert(kListNodes <= 12 * 256, "k_task_segments takes twelve nodes per thread");
 
-__global__ __launch_bounds__(256) void k_task_count(int64_t P, const uint64_t* __restrict__ n_live,
-                                                    const uint32_t* __restrict__ order,
-                                                    const float4* __restrict__ disc, const float* __restrict__ radius,
-                                                    BinTables T, uint32_t* __restrict__ tcount,
-                                                    uint32_t* __restrict__ slots, int nn, uint32_t* __restrict__ hist) {
-  __shared__ TopNodes S;
-  __shared__ uint32_t s_cnt[kHistNodes];
+// Where k_task_walk leaves its runs: block v's first `fixed` tasks at
+// [v * fixed], the others at obase[v] of the shared overflow part, allocated
+// by one atomic (only workgroups of wide Gaussians have any).  Tasks past the
+// overflow part are not written: the total then exceeds the task capacity
+// (ocap is that capacity) and nothing is emitted.
+struct TaskStage {
+  uint32_t* g;      // Gaussian of each task
+  uint16_t* n;      // its node within the group
+  uint32_t* og;
+  uint16_t* on;
+  uint32_t* cnt;    // [blocks]
+  uint64_t* obase;  // [blocks]
+  uint64_t* ocount; // overflow tasks so far
+  int64_t ocap;
+  int fixed;
+};
+
+// The 256-Gaussian blocks b of a workgroup: first, first + step, ... below
+// the live ones.  XCD h mod 8 takes runs of 32 consecutive numbers, whose
+// 4-byte entries of a histogram row share a cache line, and the workgroups of a
+// bounded grid (what is resident at once) loop: a launch of one workgroup per 256 Gaussians of
+// the scene spent tens of microseconds on starting idle ones when a narrow
+// view keeps an eighth of the scene.
+constexpr unsigned kWalkGrid = 768, kPlaceGrid = 1024;
+static unsigned walk_grid(unsigned G, unsigned most) { return G < most ? (G + 255u) & ~255u : most; }
+__device__ __forceinline__ int64_t walk_first(uint32_t h) {
+  const uint32_t x = h & 7u, k = h >> 3;
+  return (int64_t)(((k >> 5) * 8u + x) * 32u + (k & 31u));
+}
+
+// Balanced tree walk.  The lanes of a wave share a stack of (Gaussian, node)
+// entries that passed: up to 64 at a time leave it, each lane tests one child
+// of sixteen of them in turn, and the children that pass go back on it, or,
+// at the split level, set the Gaussian's bit in the node's row of a bit matrix
+// in LDS.  A Gaussian next to the camera reaches hundreds of nodes, and a lane
+// that walked them alone held up its wave: 250K Gaussians seen by a 75-degree
+// pinhole at Nside 1024 took 105 us to count and 219 us to place, one lane's
+// chain of dependent tests; the shared stack makes that 38 and 11 us (1M
+// Gaussians on the full sphere at Nside 512: 72 + 122 us became 95 + 30 us).
+// Four lanes to a parent read its four children's caps as one 64-byte line.
+// The same nodes pass as in coarse_nodes: the faces, which that walk does not
+// test, are tested with a margin (a face's cap contains its descendants'), so
+// they only save work.
+//
+// A task's place in its node's row is the number of set bits before its own.
+// The waves also list their tasks: a workgroup whose lists hold them all
+// takes the tasks from there.  The others (wide Gaussians) read the matrix
+// back with a lane per 32-bit word, the eight words of a node side by side, so
+// that a few nodes that every Gaussian reaches are spread over the workgroup
+// (with a thread per three nodes one thread wrote hundreds of tasks one by one).
+//
+// Stack bound: entries leave 64 at a time and push at most 256 of the next
+// deeper levels, so going up the stack each batch holds deeper levels only, and
+// at most 192 entries remain of each of the levels 1 to ls - 1 above at most 63
+// faces: 63 + 192 + 192 + 256 = 703 at ls = 4.
+// Bound by VALU issue (1,690 instructions per 64 Gaussians, 43 of the 95 us)
+// and latency; 52 KB of LDS, three workgroups per CU.
+constexpr int kWalkRow = kWalkGroup + 8;  // pitch of the bit matrix: its eight words of a node in different banks
+constexpr int kWalkStack = 704;  // entries per wave: Gaussian of the wave << 10 | heap index
+constexpr int kWalkList = 1024;  // tasks listed per wave: node << 6 | Gaussian of the wave
+struct WalkLds {
+  float4 cap[kTopNodes];  // levels 0..2: centre and sin(R/2)
+  float cr[kTopNodes];    // cos(R/2); NaN for inactive nodes, which then pass no test
+  uint32_t bits[8][kWalkRow];
+  uint32_t cnt[kWalkGroup];  // tasks per node
+  uint16_t list[4][kWalkList];
+  uint16_t stack[4][kWalkStack];
+  union {
+    struct {
+      float4 disc[256];
+      float cg[256];
+    };
+    struct {  // after the walk
+      uint32_t start[kWalkGroup];  // the node's first place in the run
+      uint32_t gid[256];
+    };
+  };
+};
+__global__ __launch_bounds__(256) void k_task_walk(const uint64_t* __restrict__ n_live,
+                                                   const uint32_t* __restrict__ order,
+                                                   const float4* __restrict__ disc, BinTables T, int nn, int64_t G,
+                                                   uint32_t* __restrict__ hist, TaskStage st) {
+  __shared__ WalkLds s;
+  __shared__ uint32_t s_w[4], s_listed[4];
+  __shared__ uint64_t s_ob;
   const int64_t n_in = (int64_t)*n_live;
-  if ((int64_t)blockIdx.x * blockDim.x >= n_in) return;
-  const int ntop = load_top_nodes(T, S);
-  for (int n = threadIdx.x; n < nn; n += blockDim.x) s_cnt[n] = 0u;
-  __syncthreads();
-  const float srmax = top_srmax(S, ntop);
-  const int gb = blockIdx.x;
-  const int64_t k = (int64_t)gb * blockDim.x + threadIdx.x;
-  if (k < n_in) {
-    const uint32_t gid = order[k];
-    float u[3], sg, cg;
-    bool ok;
-    gauss_dir(disc, radius, gid, T, u, &sg, &cg, &ok);
-    uint32_t cnt = 0;
-    if (ok) {
-      coarse_nodes(T, S, ntop, srmax, u, sg, cg, [&](int64_t i) {
-        if (cnt < (uint32_t)kSlots) slots[(int64_t)cnt * P + k] = (uint32_t)i;
-        atomicAdd(&s_cnt[i], 1u);
-        ++cnt;
-      });
-    }
-    tcount[k] = cnt;
+  const int64_t bfirst = walk_first(blockIdx.x);
+  if (bfirst * 256 >= n_in) return;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = hp_lane();
+  const int n0 = (int)blockIdx.y * kWalkGroup;
+  const int ng = nn - n0 < kWalkGroup ? nn - n0 : kWalkGroup;
+  const int nroot = 12 / (int)gridDim.y, root0 = (int)blockIdx.y * nroot;  // the group's faces
+  bool any = !T.node_active;
+  if (T.node_active)
+    for (int r = 0; r < nroot; ++r) any |= T.node_active[root0 + r] != 0;
+  if (!any) {  // k_hist_rows leaves out the rows of inactive nodes
+    for (int64_t b = bfirst; b * 256 < n_in; b += gridDim.x)
+      if (tid == 0) st.cnt[(int64_t)blockIdx.y * G + b] = 0u;
+    return;
   }
-  __syncthreads();
-  const int64_t G = gridDim.x;
-  for (int n = threadIdx.x; n < nn; n += blockDim.x) hist[(int64_t)n * G + gb] = s_cnt[n];
+  const int64_t nlev = hp_level_offset(T.ls + 1);  // nodes of levels 0..ls
+  const int ntop = (int)(nlev < kTopNodes ? nlev : kTopNodes);
+  for (int t = tid; t < ntop; t += 256) {
+    const float4 c = T.cap[t];
+    const float2 h = T.sc[t];
+    const bool act = !T.node_active || T.node_active[t] != 0;
+    const float nan = __int_as_float(0x7fc00000);
+    s.cap[t] = act ? make_float4(c.x, c.y, c.z, h.x) : make_float4(nan, nan, nan, nan);
+    s.cr[t] = act ? h.y : nan;
+  }
+  const int leaf0 = (int)hp_level_offset(T.ls);  // heap index of the split level's first node
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint16_t* stack = s.stack[wv];
+  uint16_t* list = s.list[wv];
+  const float4* wdisc = s.disc + 64 * wv;
+  const float* wcg = s.cg + 64 * wv;
+  const int w8 = tid & 7;
+  const int rounds = (ng + 31) / 32;
+
+  // this block's Gaussian; the next block's is fetched during the walk
+  auto fetch = [&](int64_t b, uint32_t* id, float4* d) {
+    const int64_t k = b * 256 + tid;
+    *id = k < n_in ? order[k] : 0u;
+    *d = k < n_in ? disc[*id] : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  uint32_t gid_next;
+  float4 dg_next;
+  fetch(bfirst, &gid_next, &dg_next);
+
+  for (int64_t b = bfirst; b * 256 < n_in; b += gridDim.x) {
+    const int64_t vb = (int64_t)blockIdx.y * G + b;
+    __syncthreads();  // the previous block's reads are done
+    for (int i = tid; i < 8 * kWalkRow / 4; i += 256) reinterpret_cast<uint4*>(&s.bits[0][0])[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < kWalkGroup; i += 256) s.cnt[i] = 0u;
+    const uint32_t gid = gid_next;
+    const float4 dg = dg_next;
+    const bool live = dg.w > 0.f;
+    float sg = dg.w, cg = sqrtf(fmaxf(0.f, 1.f - dg.w * dg.w));
+    widen_half(T.wsin, T.wcos, &sg, &cg);
+    s.disc[tid] = make_float4(dg.x, dg.y, dg.z, sg);
+    s.cg[tid] = cg;
+    fetch(b + gridDim.x, &gid_next, &dg_next);
+    __syncthreads();
+    // the faces the Gaussian may reach: the angle to the face's centre at most
+    // R + theta, by cosines (their rounding, 1e-6, is far below the margin)
+    uint32_t faces = 0;
+#pragma unroll
+    for (int r = 0; r < 12; ++r) {
+      const int n = r < nroot ? root0 + r : root0;
+      const float4 c = s.cap[n];
+      const float cr = s.cr[n];
+      const float sh = fmaf(c.w, cg, cr * sg), ch = fmaf(cr, cg, -(c.w * sg));  // (R + theta) / 2
+      const float dot = fmaf(c.z, dg.z, fmaf(c.y, dg.y, c.x * dg.x));
+      faces |= live && (ch <= 1e-4f || dot >= fmaf(-2.f * sh, sh, 1.f - 1e-4f)) ? 1u << r : 0u;
+    }
+    int top = 0, f = 0, nlist = 0;
+    // a task of this lane: its bit, its node's count and the wave's list
+    auto emit = [&](bool in, int node, uint32_t g) {
+      const uint64_t em = __ballot(in);
+      if (em == 0) return;
+      if (in) {
+        atomicOr(&s.bits[2 * wv + (int)(g >> 5)][node], 1u << (g & 31u));
+        atomicAdd(&s.cnt[node], 1u);
+        const int at = nlist + (int)__popcll(em & below);
+        if (at < kWalkList) list[at] = (uint16_t)((node << 6) | (int)g);
+      }
+      nlist += (int)__popcll(em);
+    };
+    if (T.ls == 0) {
+      for (; f < 12; ++f) {
+        const float4 c = s.cap[f];
+        emit(live && hp_cap_test(c.x, c.y, c.z, c.w, s.cr[f], dg.x, dg.y, dg.z, sg, cg), f, (uint32_t)lane);
+      }
+    }
+    while (true) {
+      while (f < nroot && top < 64) {
+        const bool in = ((faces >> f) & 1u) != 0u;
+        const uint64_t m = __ballot(in);
+        if (in) stack[top + __popcll(m & below)] = (uint16_t)((lane << 10) | (root0 + f));
+        top += (int)__popcll(m);
+        ++f;
+      }
+      if (top == 0) break;
+      const int m = top < 64 ? top : 64;
+      top -= m;
+      // entry 16 r + lane / 4 of the popped ones: its child lane % 4
+      uint32_t it[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int e = 16 * r + (lane >> 2);
+        it[r] = stack[top + (e < m ? e : 0)];
+      }
+      float4 c[4], d[4];
+      float cr[4], dcg[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // children of heap node X: 4 (X + 3) .. 4 (X + 3) + 3
+        const int child = 4 * (int)((it[r] & 1023u) + 3u) + (lane & 3);
+        d[r] = wdisc[it[r] >> 10];
+        dcg[r] = wcg[it[r] >> 10];
+        if (child < kTopNodes) {
+          c[r] = s.cap[child];
+          cr[r] = s.cr[child];
+        } else {
+          c[r] = T.cap[child];
+          const float2 h = T.sc[child];
+          c[r].w = h.x;
+          cr[r] = T.node_active && !T.node_active[child] ? __int_as_float(0x7fc00000) : h.y;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (16 * r >= m) break;
+        const int child = 4 * (int)((it[r] & 1023u) + 3u) + (lane & 3);
+        const uint32_t g = it[r] >> 10;
+        // an inactive node's NaN fails both comparisons
+        const bool in = 16 * r + (lane >> 2) < m &&
+                        hp_cap_test(c[r].x, c[r].y, c[r].z, c[r].w, cr[r], d[r].x, d[r].y, d[r].z, d[r].w, dcg[r]);
+        const bool leaf = child >= leaf0;
+        const uint64_t pm = __ballot(in && !leaf);
+        if (in && !leaf) stack[top + __popcll(pm & below)] = (uint16_t)((g << 10) | (uint32_t)child);
+        top += (int)__popcll(pm);
+        emit(in && leaf, child - leaf0 - n0, g);
+      }
+    }
+    if (lane == 0) s_listed[wv] = nlist <= kWalkList;
+    __syncthreads();
+    // the node counts to the histogram, and scanned (thread t: nodes 3t .. 3t + 2)
+    s.gid[tid] = gid;
+    uint32_t cnt[3], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int n = 3 * tid + q;
+      cnt[q] = n < ng ? s.cnt[n] : 0u;
+      if (n < ng) hist[(int64_t)(n0 + n) * G + b] = cnt[q];
+      sum += cnt[q];
+    }
+    uint32_t total;
+    uint32_t pos = hpsort::block_exclusive<uint32_t>(sum, &total, s_w);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      if (3 * tid + q < ng) s.start[3 * tid + q] = pos;
+      pos += cnt[q];
+    }
+    const uint32_t fixed = (uint32_t)st.fixed;
+    if (tid == 0) {
+      st.cnt[vb] = total;
+      if (total > fixed) {
+        const uint64_t o = atomicAdd((unsigned long long*)st.ocount, (unsigned long long)(total - fixed));
+        st.obase[vb] = o;
+        s_ob = o;
+      }
+    }
+    __syncthreads();
+    const uint64_t ob = total > fixed ? s_ob : 0ull;
+    auto put = [&](uint32_t at, uint32_t g, uint32_t n) {
+      if (at < fixed) {
+        st.g[vb * fixed + at] = g;
+        st.n[vb * fixed + at] = (uint16_t)n;
+      } else if (ob + (at - fixed) < (uint64_t)st.ocap) {
+        st.og[ob + (at - fixed)] = g;
+        st.on[ob + (at - fixed)] = (uint16_t)n;
+      }
+    };
+    if (s_listed[0] & s_listed[1] & s_listed[2] & s_listed[3]) {
+      for (int t = lane; t < nlist; t += 64) {
+        const uint32_t e = list[t], n = e >> 6, g = e & 63u;
+        const int w = 2 * wv + (int)(g >> 5);
+        uint32_t rank = (uint32_t)__popc(s.bits[w][n] & ((1u << (g & 31u)) - 1u));
+#pragma unroll
+        for (int v = 0; v < 7; ++v) rank += v < w ? (uint32_t)__popc(s.bits[v][n]) : 0u;
+        put(s.start[n] + rank, s.gid[64 * wv + (int)g], n);
+      }
+    } else {
+      // word w8 of node 32 r + tid / 8: its tasks after those of the words before
+      for (int r = 0; r < rounds; ++r) {
+        const int n = 32 * r + (tid >> 3);
+        uint32_t bits = s.bits[w8][n];
+        uint32_t x = (uint32_t)__popc(bits);
+        const uint32_t own = x;
+        const uint32_t y1 = hpsort::dpp_u32<0x111, 0xf, true>(x);
+        x += w8 >= 1 ? y1 : 0u;
+        const uint32_t y2 = hpsort::dpp_u32<0x112, 0xf, true>(x);
+        x += w8 >= 2 ? y2 : 0u;
+        const uint32_t y4 = hpsort::dpp_u32<0x114, 0xf, true>(x);
+        x += w8 >= 4 ? y4 : 0u;
+        uint32_t at = (n < ng ? s.start[n] : 0u) + x - own;
+        while (bits != 0) {
+          put(at++, s.gid[32 * w8 + __builtin_ctz(bits)], (uint32_t)n);
+          bits &= bits - 1;
+        }
+      }
+    }
+  }
 }
 
 // One workgroup per node n: the histogram row hist[n][0..G) becomes its
 // exclusive scan hoff[n][0..G) (where workgroup b's tasks at node n start
-// among the node's tasks) and rowtot[n] the node's task count.  The node
-// offsets (an exclusive scan of rowtot) follow in k_task_segments.
-// Rows have room for G workgroups; those of the *n_live Gaussians are filled.
+// among the node's tasks) and rowtot[n] the node's task count (a Gaussian has
+// at most one task per node, so 32 bits hold a row).  The node offsets (an
+// exclusive scan of rowtot) follow in k_task_segments.  Rows have room for G
+// workgroups; those of the *n_live Gaussians are filled, and none where the
+// node (active: the split level's flags, or null) is inactive.
 __global__ __launch_bounds__(256) void k_hist_rows(const uint32_t* __restrict__ hist, int64_t G,
-                                                   const uint64_t* __restrict__ n_live, uint64_t* __restrict__ hoff,
+                                                   const uint64_t* __restrict__ n_live,
+                                                   const uint8_t* __restrict__ active, uint32_t* __restrict__ hoff,
                                                    uint64_t* __restrict__ rowtot) {
-  __shared__ uint64_t s_w[4];
-  const int64_t g_live = (int64_t)((*n_live + 255) / 256);
+  __shared__ uint32_t s_w[4];
   constexpr int kItems = 16;
+  if (active && !active[blockIdx.x]) {
+    if (threadIdx.x == 0) rowtot[blockIdx.x] = 0ull;
+    return;
+  }
+  const int64_t g_live = (int64_t)((*n_live + 255) / 256);
   const uint32_t* row = hist + (int64_t)blockIdx.x * G;
-  uint64_t* out = hoff + (int64_t)blockIdx.x * G;
-  uint64_t carry = 0;
+  uint32_t* out = hoff + (int64_t)blockIdx.x * G;
+  uint32_t carry = 0;
   for (int64_t t0 = 0; t0 < g_live; t0 += 256 * kItems) {
     const int64_t j0 = t0 + (int64_t)kItems * threadIdx.x;
-    uint32_t v[kItems];
-    uint64_t acc = 0;
+    uint32_t v[kItems], acc = 0;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
       v[k] = j0 + k < g_live ? row[j0 + k] : 0u;
       acc += v[k];
     }
-    uint64_t tot;
-    uint64_t ex = hpsort::block_exclusive<uint64_t>(acc, &tot, s_w) + carry;
+    uint32_t tot;
+    uint32_t ex = hpsort::block_exclusive<uint32_t>(acc, &tot, s_w) + carry;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
       if (j0 + k < g_live) out[j0 + k] = ex;
@@ -415,108 +685,66 @@ __global__ __launch_bounds__(256) void k_hist_rows(const uint32_t* __restrict__ 
   if (threadIdx.x == 0) rowtot[blockIdx.x] = carry;
 }
 
-// Dynamic LDS per node: the workgroup's first slot (8 B), 256 membership
-// bits (which of the workgroup's Gaussians have a task at the node), the
-// node's first place in the workgroup's staging run (4 B) and the bit counts
-// before each of the 8 words (8 x 1 B): 52 B.
-constexpr int kScatterLdsPerNode = 52;
-// tasks of one workgroup staged in LDS in node order, then written out in
-// runs; a workgroup with more writes its tasks directly
-constexpr int kStage = 2048;
-
-__global__ __launch_bounds__(256) void k_task_scatter(int64_t P, const uint64_t* __restrict__ n_live,
-                                                      const uint32_t* __restrict__ order,
-                                                      const float4* __restrict__ disc,
-                                                      const float* __restrict__ radius, BinTables T,
-                                                      const uint32_t* __restrict__ tcount,
-                                                      const uint32_t* __restrict__ slots, int nn,
-                                                      const uint64_t* __restrict__ hoff,
-                                                      const uint64_t* __restrict__ node_off, int64_t cap_t,
-                                                      uint32_t* __restrict__ task_g) {
-  extern __shared__ uint64_t s_dyn[];
-  uint64_t* s_off = s_dyn;                            // [nn]
-  uint32_t* s_bits = (uint32_t*)(s_dyn + nn);         // [nn][8]
-  uint32_t* s_start = s_bits + 8 * nn;                // [nn]
-  uint8_t* s_pre = (uint8_t*)(s_start + nn);          // [nn][8]
-  __shared__ TopNodes S;
-  __shared__ uint32_t s_gid[kStage];
-  __shared__ uint16_t s_node[kStage];
-  __shared__ uint32_t s_w[4];
+// Every staged run to its nodes' places in the task list (the blocks of
+// k_task_walk, in the same order); also the node of every chunk of 64 tasks,
+// nodes strided over the workgroups.  Bound by HBM: 6 B read and 4 B written
+// per task.
+constexpr int kPlaceThreads = 512, kPlaceIlp = 4;
+__global__ __launch_bounds__(kPlaceThreads) void k_task_place(const uint64_t* __restrict__ n_live, int nn, int64_t G,
+                                                              TaskStage st, const uint32_t* __restrict__ hoff,
+                                                              const uint64_t* __restrict__ node_off, int64_t cap_t,
+                                                              uint32_t* __restrict__ task_g,
+                                                              const uint32_t* __restrict__ choff,
+                                                              uint32_t* __restrict__ cnode) {
+  __shared__ uint64_t s_first[kWalkGroup];
+  for (int64_t n = (int64_t)blockIdx.y * gridDim.x + blockIdx.x; n < nn; n += (int64_t)gridDim.x * gridDim.y) {
+    const uint32_t c1 = choff[n + 1];
+    for (uint32_t c = choff[n] + threadIdx.x; c < c1; c += blockDim.x) cnode[c] = (uint32_t)n;
+  }
   const int64_t n_in = (int64_t)*n_live;
-  if ((int64_t)blockIdx.x * blockDim.x >= n_in) return;
-  const int ntop = load_top_nodes(T, S);
-  const int64_t G = gridDim.x;
-  for (int n = threadIdx.x; n < nn; n += blockDim.x) s_off[n] = node_off[n] + hoff[(int64_t)n * G + blockIdx.x];
-  for (int i = threadIdx.x; i < 8 * nn; i += blockDim.x) s_bits[i] = 0u;
-  __syncthreads();
-  const float srmax = top_srmax(S, ntop);
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = k < n_in;
-  const uint32_t cnt = live ? tcount[k] : 0u;
-  const uint32_t gid = live ? order[k] : 0u;
-  const int w = threadIdx.x >> 5;
-  const uint32_t bit = 1u << (threadIdx.x & 31);
-  // the Gaussian's nodes: from the count walk's slots, or walked again when
-  // it had more than kSlots
-  auto each_node = [&](auto&& f) {
-    if (cnt <= (uint32_t)kSlots) {
-      for (uint32_t j = 0; j < cnt; ++j) f((int64_t)slots[(int64_t)j * P + k]);
-      return;
-    }
-    float u[3], sg, cg;
-    bool ok;
-    gauss_dir(disc, radius, gid, T, u, &sg, &cg, &ok);
-    if (ok) coarse_nodes(T, S, ntop, srmax, u, sg, cg, f);
-  };
-  if (cnt) each_node([&](int64_t i) { atomicOr(&s_bits[8 * i + w], bit); });
-  __syncthreads();
-  // per node (thread t: nodes 4t .. 4t + 3): counts before each word, and
-  // the node's place in the workgroup's node-ordered run
-  uint32_t tot[4], sum = 0;
+  const int n0 = (int)blockIdx.y * kWalkGroup;
+  for (int64_t b = walk_first(blockIdx.x); b * 256 < n_in; b += gridDim.x) {
+    const int64_t vb = (int64_t)blockIdx.y * G + b;
+    const uint32_t total = st.cnt[vb], fixed = (uint32_t)st.fixed;
+    if (total == 0) continue;
+    const uint64_t ob = total > fixed ? st.obase[vb] : 0ull;
+    // task t of the run; tasks that the overflow part did not hold are past tmax
+    const uint64_t room = ob < (uint64_t)st.ocap ? (uint64_t)st.ocap - ob : 0ull;
+    const uint32_t tmax = total > fixed && total - fixed > room ? fixed + (uint32_t)room : total;
+    auto node = [&](uint32_t t) { return (uint32_t)(t < fixed ? st.n[vb * fixed + t] : st.on[ob + (t - fixed)]); };
+    __syncthreads();  // the previous run's reads are done
+    // kPlaceIlp tasks of a thread at a time, their loads all in flight: the
+    // runs of the widest Gaussians are tens of times the others' length
+    constexpr uint32_t kStep = kPlaceThreads * kPlaceIlp;
+    for (uint32_t t0 = threadIdx.x; t0 < tmax; t0 += kStep) {
+      uint32_t n[kPlaceIlp], before[kPlaceIlp];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = 4 * (int)threadIdx.x + q;
-    uint32_t a = 0;
-    if (n < nn) {
+      for (int j = 0; j < kPlaceIlp; ++j) {
+        const uint32_t t = t0 + j * kPlaceThreads;
+        n[j] = t < tmax ? node(t) : 0u;
+        before[j] = t > 0 && t < tmax ? node(t - 1) : ~0u;
+      }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        s_pre[8 * n + j] = (uint8_t)a;
-        a += (uint32_t)__popc(s_bits[8 * n + j]);
+      for (int j = 0; j < kPlaceIlp; ++j) {
+        const uint32_t t = t0 + j * kPlaceThreads;
+        if (t < tmax && n[j] != before[j]) s_first[n[j]] = node_off[n0 + n[j]] + hoff[(int64_t)(n0 + n[j]) * G + b] - t;
       }
     }
-    tot[q] = a;
-    sum += a;
-  }
-  uint32_t total;
-  uint32_t ex = hpsort::block_exclusive<uint32_t>(sum, &total, s_w);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = 4 * (int)threadIdx.x + q;
-    if (n < nn) s_start[n] = ex;
-    ex += tot[q];
-  }
-  __syncthreads();
-  const bool staged = total <= (uint32_t)kStage;
-  if (cnt) {
-    each_node([&](int64_t i) {
-      const uint32_t r = (uint32_t)s_pre[8 * i + w] + (uint32_t)__popc(s_bits[8 * i + w] & (bit - 1u));
-      if (staged) {
-        const uint32_t lp = s_start[i] + r;
-        s_gid[lp] = gid;
-        s_node[lp] = (uint16_t)i;
-      } else {
-        const uint64_t pos = s_off[i] + r;
-        if (pos < (uint64_t)cap_t) task_g[pos] = gid;
-      }
-    });
-  }
-  if (staged) {
     __syncthreads();
-    // consecutive threads write consecutive places of each node's run
-    for (uint32_t t = threadIdx.x; t < total; t += blockDim.x) {
-      const int n = s_node[t];
-      const uint64_t pos = s_off[n] + (t - s_start[n]);
-      if (pos < (uint64_t)cap_t) task_g[pos] = s_gid[t];
+    for (uint32_t t0 = threadIdx.x; t0 < tmax; t0 += kStep) {
+      uint32_t n[kPlaceIlp], g[kPlaceIlp];
+#pragma unroll
+      for (int j = 0; j < kPlaceIlp; ++j) {
+        const uint32_t t = t0 + j * kPlaceThreads;
+        n[j] = t < tmax ? node(t) : 0u;
+        g[j] = t >= tmax ? 0u : (t < fixed ? st.g[vb * fixed + t] : st.og[ob + (t - fixed)]);
+      }
+#pragma unroll
+      for (int j = 0; j < kPlaceIlp; ++j) {
+        const uint32_t t = t0 + j * kPlaceThreads;
+        const uint64_t pos = t < tmax ? s_first[n[j]] + t : (uint64_t)cap_t;
+        if (pos < (uint64_t)cap_t) task_g[pos] = g[j];
+      }
     }
   }
 }
@@ -533,24 +761,26 @@ __global__ __launch_bounds__(256) void k_task_segments(int nn, const uint64_t* _
                                                        uint32_t* __restrict__ choff, uint64_t* __restrict__ ncol) {
   __shared__ uint64_t s_w64[4];
   __shared__ uint32_t s_w[4];
-  // nodes 4t .. 4t + 3 of thread t
-  uint64_t cnt[4], sum = 0;
+  // thread t takes the `per` consecutive nodes from per * t (at most kPer)
+  constexpr int kPer = kListNodes / 256;
+  const int per = (nn + 255) / 256;
+  uint64_t cnt[kPer], sum = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = 4 * (int)threadIdx.x + q;
-    cnt[q] = n < nn ? rowtot[n] : 0ull;
+  for (int q = 0; q < kPer; ++q) {
+    const int n = per * (int)threadIdx.x + q;
+    cnt[q] = q < per && n < nn ? rowtot[n] : 0ull;
     sum += cnt[q];
   }
   uint64_t tot;
   uint64_t pre = hpsort::block_exclusive<uint64_t>(sum, &tot, s_w64);
   const bool ov = tot > (uint64_t)cap_t;
   const uint64_t lim = ov ? (uint64_t)cap_t : tot;
-  uint32_t nch[4], csum = 0;
+  uint32_t nch[kPer], csum = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = 4 * (int)threadIdx.x + q;
+  for (int q = 0; q < kPer; ++q) {
+    const int n = per * (int)threadIdx.x + q;
     nch[q] = 0u;
-    if (n < nn) {
+    if (q < per && n < nn) {
       node_off[n] = pre;
       uint64_t s0 = pre, s1 = pre + cnt[q];
       s0 = s0 < lim ? s0 : lim;
@@ -565,9 +795,9 @@ __global__ __launch_bounds__(256) void k_task_segments(int nn, const uint64_t* _
   uint32_t total;
   uint32_t ex = hpsort::block_exclusive<uint32_t>(csum, &total, s_w);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = 4 * (int)threadIdx.x + q;
-    if (n < nn) choff[n] = ex;
+  for (int q = 0; q < kPer; ++q) {
+    const int n = per * (int)threadIdx.x + q;
+    if (q < per && n < nn) choff[n] = ex;
     ex += nch[q];
   }
   if (threadIdx.x == 0) {
@@ -1018,15 +1248,19 @@ static unsigned fine_grid(int64_t nt) {
 // cone, since every Gaussian would pass.  The cone's pass also writes the
 // keys, so that the scatter drops the same Gaussians.  Bound by HBM: 4 B read
 // per Gaussian, 24 B read and written with a cone.
-// Also marks the count unfinished (see depth_order).
+// Also marks the count unfinished (see depth_order) and empties the walk's
+// overflow part.
 constexpr uint32_t kNoDepth = 0x7f800000u;  // +inf
 template <bool CONE>
 __global__ __launch_bounds__(256) void k_depth_hist(const uint32_t* depth, const float4* __restrict__ disc, int64_t P,
                                                     const float* __restrict__ cone, float wsin, float wcos,
                                                     uint32_t* keys, uint32_t* __restrict__ hist,
-                                                    int64_t* __restrict__ n_pairs) {
+                                                    int64_t* __restrict__ n_pairs, uint64_t* __restrict__ n_over) {
   __shared__ uint32_t s_h[256];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_pairs = INT64_MAX;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *n_pairs = INT64_MAX;
+    *n_over = 0ull;
+  }
   s_h[threadIdx.x] = 0u;
   __syncthreads();
   float sr = 1.f, cr = 0.f;
@@ -1064,10 +1298,10 @@ static hp_status depth_order(const HpProjView& pv, int64_t P, const float* cone,
   const dim3 grid(hpsort::radix_grid(P));
   if (cone)
     hipLaunchKernelGGL(k_depth_hist<true>, grid, dim3(256), 0, s, depth, pv.disc, P, cone, T.wsin, T.wcos, w.dkey, hist,
-                       n_pairs);
+                       n_pairs, w.n_over);
   else
     hipLaunchKernelGGL(k_depth_hist<false>, grid, dim3(256), 0, s, depth, pv.disc, P, cone, T.wsin, T.wcos, w.dkey, hist,
-                       n_pairs);
+                       n_pairs, w.n_over);
   HP_CHECK_LAUNCH();
   const hpsort::RadixFirst first{cone ? w.dkey : depth, kNoDepth, w.n_live};
   return hpsort::radix_sort(w.dkey, w.order, nullptr, P, 32, w.sort_ws, s, nullptr, nullptr, &first);
@@ -1240,33 +1474,45 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
     }
     // until the count below completes, *n_pairs says that nothing may be
     // emitted (set by the depth sort's first kernel)
-    if (sw.nn <= kHistNodes) {
-      // tasks written in node order straight from the walk (no task sort);
-      // the histogram lives in task_n and its row scans, node counts and node
-      // offsets in poff, which this path does not otherwise use
-      // (nn x G + 2 nn <= 3 (P + 255) + 1536 <= task capacity)
+    if (sw.nn <= kListNodes) {
+      // tasks written in node order straight from the walk (no task sort).
+      // Buffers that this path does not otherwise use hold its tables: the
+      // histogram in task_n (nn x G <= 12 (P + 255) <= task capacity), its row
+      // scans, the node totals and offsets in poff, the staged runs in the
+      // task sort's workspace (4096 tasks per 256 Gaussians, 16 P + 4080 <=
+      // task capacity), their overflow in wcol (6 of its 8 B per task) and
+      // their counts in pmask.
       HP_TRY(depth_order(pv, P, cone, T, w, n_pairs, s));
       const unsigned G = hp_blocks(P, 256);
       const int nni = (int)sw.nn;
+      const unsigned groups = (unsigned)((nni + kWalkGroup - 1) / kWalkGroup);
       uint32_t* hist = w.task_n;
-      uint64_t* hoff = w.poff;
-      hipLaunchKernelGGL(k_task_count, dim3(G), dim3(256), 0, s, P, (const uint64_t*)w.n_live,
-                         (const uint32_t*)w.order, pv.disc, pv.radius, T, w.tcount, sw.slots, nni, hist);
-      HP_CHECK_LAUNCH();
-      // per node: the row scan of the histogram and the node's task count
-      // (after the histogram in poff), then the node offsets
-      uint64_t* rowtot = hoff + (int64_t)nni * G;
+      uint32_t* hoff = (uint32_t*)w.poff;
+      uint64_t* rowtot = w.poff + ((int64_t)nni * G + 1) / 2;
       uint64_t* node_off = rowtot + nni;
+      TaskStage st;
+      st.g = (uint32_t*)sw.tsort_ws;
+      st.n = (uint16_t*)(st.g + w.cap_t);
+      st.og = (uint32_t*)sw.wcol;
+      st.on = (uint16_t*)(st.og + w.cap_t);
+      st.obase = w.pmask;
+      st.cnt = (uint32_t*)(w.pmask + (int64_t)G * groups);
+      st.ocount = w.n_over;
+      st.ocap = w.cap_t;
+      st.fixed = kStageFixed / (int)groups;
+      const dim3 wg(walk_grid(G, kWalkGrid), groups), pg(walk_grid(G, kPlaceGrid), groups);
+      hipLaunchKernelGGL(k_task_walk, wg, dim3(256), 0, s, (const uint64_t*)w.n_live, (const uint32_t*)w.order, pv.disc,
+                         T, nni, (int64_t)G, hist, st);
+      HP_CHECK_LAUNCH();
       hipLaunchKernelGGL(k_hist_rows, dim3(nni), dim3(256), 0, s, (const uint32_t*)hist, (int64_t)G,
-                         (const uint64_t*)w.n_live, hoff, rowtot);
+                         (const uint64_t*)w.n_live, T.node_active ? T.node_active + hp_level_offset(ls) : nullptr, hoff,
+                         rowtot);
       HP_CHECK_LAUNCH();
       hipLaunchKernelGGL(k_task_segments, dim3(1), dim3(256), 0, s, nni, (const uint64_t*)rowtot, node_off, w.cap_t,
                          depth, w.t_total, w.nt, w.over, sw.seg, sw.choff, w.ncol);
       HP_CHECK_LAUNCH();
-      hipLaunchKernelGGL(k_task_scatter, dim3(G), dim3(256), (size_t)nni * kScatterLdsPerNode, s, P,
-                         (const uint64_t*)w.n_live, (const uint32_t*)w.order, pv.disc, pv.radius, T, (const uint32_t*)w.tcount,
-                         (const uint32_t*)sw.slots, nni, (const uint64_t*)hoff, (const uint64_t*)node_off, w.cap_t,
-                         w.task_g);
+      hipLaunchKernelGGL(k_task_place, pg, dim3(kPlaceThreads), 0, s, (const uint64_t*)w.n_live, nni, (int64_t)G, st, (const uint32_t*)hoff,
+                         (const uint64_t*)node_off, w.cap_t, w.task_g, (const uint32_t*)sw.choff, sw.cnode);
       HP_CHECK_LAUNCH();
     } else {
       HP_TRY(bin_tasks(pv, P, cone, T, prm->bin_guard, w, sw.slots, n_pairs, s));
@@ -1295,9 +1541,9 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
       // is written), scanned in tile-major order into output slots
       hipLaunchKernelGGL(k_col_count, dim3(1), dim3(1), 0, s, (const uint32_t*)sw.choff, nn, depth, w.ncol);
       HP_CHECK_LAUNCH();
+      hipLaunchKernelGGL(k_chunk_nodes, dim3(nn), dim3(256), 0, s, (const uint32_t*)sw.choff, sw.cnode);
+      HP_CHECK_LAUNCH();
     }
-    hipLaunchKernelGGL(k_chunk_nodes, dim3(nn), dim3(256), 0, s, (const uint32_t*)sw.choff, sw.cnode);
-    HP_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_bin_cols, dim3(chunk_grid(sw.nchunk_max)), dim3(256), 0, s, (const uint32_t*)sw.choff, nn,
                        (const uint32_t*)sw.seg, (const uint32_t*)sw.cnode, (const uint32_t*)w.task_g, pv.disc, T,
                        sw.wcol, sw.cnt);
