@@ -137,9 +137,8 @@ HP_HD uint32_t hp_spread_bits(uint32_t v) {
   return v;
 }
 HP_HD void hp_nest_xyf(int order, int64_t p, int* x, int* y, int* f) {
-  int64_t npf = (int64_t)1 << (2 * order);
-  *f = (int)(p / npf);
-  uint32_t q = (uint32_t)(p - (int64_t)(*f) * npf);
+  *f = (int)(p >> (2 * order));
+  const uint32_t q = (uint32_t)p & ((1u << (2 * order)) - 1u);
   *x = (int)hp_compact_bits(q);
   *y = (int)hp_compact_bits(q >> 1);
 }
@@ -147,35 +146,44 @@ HP_HD int64_t hp_xyf_nest(int order, int x, int y, int f) {
   return ((int64_t)f << (2 * order)) + (int64_t)(hp_spread_bits((uint32_t)x) | (hp_spread_bits((uint32_t)y) << 1));
 }
 
-// Pixel-centre direction in the camera frame (pole = camera +y, longitude
-// omega = atan2(t_x, t_z)): t = (sin(theta) sin(phi), z, sin(theta) cos(phi)).
+// Pixel-centre position: z, sin(theta) and the longitude phi (not wrapped).
 // Face f: row f/4 sets the ring of the face's southern corner (rows 2, 3, 4
 // in units of Nside); column f%4 sets its longitude (odd multiples of pi/4 for
 // the polar rows, multiples of pi/2 for the equatorial row).
-__device__ __forceinline__ void hp_pix_dir(int order, int64_t p, double* t) {
+// Orders up to HP_MAX_ORDER: N^2 and 8 N fit 32 bits.
+__device__ __forceinline__ void hp_pix_pos(int order, int64_t p, double* pz, double* psth, double* pphi) {
   int x, y, f;
   hp_nest_xyf(order, p, &x, &y, &f);
-  const int64_t N = (int64_t)1 << order;
+  const int N = 1 << order;
   const int row = f >> 2, col = f & 3;
-  const int64_t ring = (int64_t)(row + 2) * N - x - y - 1;   // 1 .. 4N-1 from the north pole
-  const int64_t lon_units = (row == 1) ? 2 * col : 2 * col + 1; // face centre longitude in pi/4
+  const int ring = (row + 2) * N - x - y - 1;               // 1 .. 4N-1 from the north pole
+  const int lon_units = (row == 1) ? 2 * col : 2 * col + 1; // face centre longitude in pi/4
   double z, sth, phi;
   if (ring < N || ring > 3 * N) {
-    const int64_t nr = ring < N ? ring : 4 * N - ring;        // ring index counted from its pole
+    const int nr = ring < N ? ring : 4 * N - ring;          // ring index counted from its pole
     const double tmp = (double)(nr * nr) / (3.0 * (double)(N * N));
     z = ring < N ? 1.0 - tmp : tmp - 1.0;
     sth = sqrt(tmp * (2.0 - tmp));
     // position along the ring: nr pixels per face, centred on the face longitude
-    int64_t jp = (lon_units * nr + x - y + 1) / 2;           // 1-based within ring (may wrap)
+    const int jp = (lon_units * nr + x - y + 1) / 2;        // 1-based within ring (may wrap)
     phi = ((double)jp - 0.5) * (M_PI / 2.0) / (double)nr;
   } else {
     z = (double)(2 * N - ring) * (2.0 / (3.0 * (double)N));
     sth = sqrt((1.0 - z) * (1.0 + z));
-    const int s = (int)((ring - N) & 1);
-    int64_t jp = (lon_units * N + x - y + 1 + s) / 2;
+    const int s = (ring - N) & 1;
+    const int jp = (lon_units * N + x - y + 1 + s) / 2;
     phi = ((double)jp - 0.5 * (1 + s)) * (M_PI / 2.0) / (double)N;
   }
-  double sp, cp;
+  *pz = z;
+  *psth = sth;
+  *pphi = phi;
+}
+
+// Pixel-centre direction in the camera frame (pole = camera +y, longitude
+// omega = atan2(t_x, t_z)): t = (sin(theta) sin(phi), z, sin(theta) cos(phi)).
+__device__ __forceinline__ void hp_pix_dir(int order, int64_t p, double* t) {
+  double z, sth, phi, sp, cp;
+  hp_pix_pos(order, p, &z, &sth, &phi);
   sincos(phi, &sp, &cp);
   t[0] = sth * sp;
   t[1] = z;

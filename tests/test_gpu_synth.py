@@ -98,3 +98,24 @@ def test_round_trip_at_benchmark_grid(R):
     const = torch.full_like(field, 0.375)
     im2 = R.sphere_to_image(const, c, 1024, 512)
     assert (im2 - 0.375).abs().max().item() < 1e-6
+
+
+@pytest.mark.parametrize("W,H", [(1, 1), (3, 2), (255, 7), (256, 6), (257, 5), (700, 350)])
+@pytest.mark.parametrize("order", [0, 1, 2, 3, 5, 6])
+def test_panorama_at_coarse_orders_and_row_edges(R, order, W, H):
+    """Panoramas whose rows end at, before and behind a wave's 256 pixels, on
+    grids coarse enough that neighbouring rings lie beyond the series of the
+    ring weights, against the oracle in both directions."""
+    import torch
+    from paper_2606_29794_amd.raster import Camera
+    cam = SC.make_camera(np.random.default_rng(9), order, SC.CAM_FULL)
+    c, act, rng = Camera.from_dict(cam), O.mask(cam), np.random.default_rng(order)
+    img, photo = rng.random((3, act.size)).astype(np.float32), rng.random((3, H, W)).astype(np.float32)
+    out, valid = R.sphere_to_image(torch.as_tensor(img, device="cuda"), c, W, H, want_valid=True)
+    back = R.image_to_sphere(torch.as_tensor(photo, device="cuda"), c)
+    torch.cuda.synchronize()
+    assert valid.cpu().numpy().all()
+    ref, _ = O.sphere_to_image(cam, act, img.astype(np.float64), W, H)
+    ref2, _ = O.image_to_sphere(cam, act, photo.astype(np.float64), W, H)
+    assert np.abs(out.cpu().numpy() - ref).max() < 2e-6
+    assert np.abs(back.cpu().numpy() - ref2).max() < 2e-6
