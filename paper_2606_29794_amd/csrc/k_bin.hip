@@ -74,6 +74,10 @@ static BinWs bin_ws(void* base, int64_t P) {
   return w;
 }
 
+// pmask holds 8 B for each of the 16 P + 2^20 tasks; the sorted emission uses it
+// for counts of its COUNT phase only
+void* hp_bin_spare(void* ws, int64_t P) { return bin_ws(ws, P).pmask; }
+
 // tasks kept and the overflow flag, from the scanned task total
 __global__ void k_task_clamp(const uint64_t* __restrict__ t_total, int64_t cap_t, uint64_t* __restrict__ nt,
                              uint32_t* __restrict__ over) {

@@ -30,8 +30,7 @@ constexpr int kMaxRings = 31;   // rings crossing one tile at f = 16
 struct QueryArgs {
   int mode, kq, fl, order_t;
   const int32_t* active_tiles;
-  const float4* disc;   // (direction, sin((r_s + guard) / 2)) per Gaussian
-  const float* radius;
+  const float4* gauss;  // per Gaussian what the test reads (k_query_gauss)
   uint32_t* vals;
   uint32_t* ranges;
   const int64_t* n_pairs;
@@ -93,11 +92,12 @@ __device__ void pix_ring(int kq, int64_t p, int64_t* ring, int* pos, int* x_minu
 // from omega to the run's interval widened by one step on both sides,
 // [lambda_first - step, lambda_last + step], is below d_omega.
 struct RingSlot {
-  float sh, ch;    // sin, cos of half the ring's latitude
+  float sh, ch;    // sin, cos of half the ring's latitude; (4, 0), outside every
+                   // disc's z range, when the tile has no pixel on the ring
   float clat;      // cos of its latitude
   float sm, cm;    // sin, cos of half the widened interval's middle longitude
-  float shw, chw;  // sin, cos of half its half-width
-  int whole;       // the widened interval covers the ring (or the tile has no pixel on it: -1)
+  float shw, chw;  // sin, cos of half its half-width; shw = 2, which holds every
+                   // longitude, when it covers the ring
 };
 
 // RING membership of the tile for a Gaussian with direction u and
@@ -110,54 +110,119 @@ struct RingSlot {
 // small angle enters as the sine of its half, formed as a difference of
 // products of half-angle sines and cosines: no cancellation for small discs,
 // and no transcendental per ring.
-__device__ __forceinline__ bool ring_hit(const RingSlot* S, int nslot, float ux, float uy, float uz, float hrs) {
-  const float clat_c = sqrtf(fmaf(ux, ux, uz * uz));
+// The Gaussian's part of the test: cos(lat_c), (cos, sin) of half the latitude
+// and of half the longitude of its centre, sin(r_s / 2) and its square.
+struct RingGauss {
+  float cc, sc, sw, cw, clat, srs, hrs;
+};
+__device__ __forceinline__ RingGauss ring_gauss(float4 disc, float rs) {
+  RingGauss G;
+  const float hs = sinf(0.5f * rs);
+  G.hrs = hs * hs;
+  G.srs = sqrtf(G.hrs);
+  G.clat = sqrtf(fmaf(disc.x, disc.x, disc.z * disc.z));
   // half of the centre's latitude: its cosine is at least 1/sqrt(2)
-  const float cc = sqrtf(fmaf(0.5f, clat_c, 0.5f));
-  const float sc = uy / (2.f * cc);
-  const float srs = sqrtf(hrs);
-  float sw, cw;  // half of the centre's longitude
-  sincosf(0.5f * atan2f(ux, uz), &sw, &cw);
-  for (int j = 0; j < nslot; ++j) {
-    const RingSlot r = S[j];
-    if (r.whole < 0) continue;
-    const float sd = fmaf(r.sh, cc, -(r.ch * sc));  // sin((lat_r - lat_c) / 2)
-    if (fabsf(sd) > srs) continue;                  // outside the disc's z range
-    const float num = fmaf(-sd, sd, hrs);
-    const float den = clat_c * r.clat;
-    if (num >= den) return true;   // the whole ring lies in the disc (also at the poles)
-    if (!(num > 0.f)) continue;    // d_omega = 0: no pixel
-    if (r.whole) return true;
-    // y = |omega - middle| reduced to [0, pi]: sin(y / 2), cos(y / 2)
-    const float a = fabsf(fmaf(sw, r.cm, -(cw * r.sm)));
-    const float b = fabsf(fmaf(cw, r.cm, sw * r.sm));
-    if (a <= r.shw) return true;   // inside the widened interval
-    const float sdist = fmaf(a, r.chw, -(b * r.shw));  // sin((y - half-width) / 2)
-    if (den * (sdist * sdist) < num) return true;
+  G.cc = sqrtf(fmaf(0.5f, G.clat, 0.5f));
+  G.sc = disc.y / (2.f * G.cc);
+  sincosf(0.5f * atan2f(disc.x, disc.z), &G.sw, &G.cw);
+  return G;
+}
+// The lanes of the wave whose Gaussian hits the ring.  Predicates are combined
+// as wave masks (single compares, scalar logic): as lane booleans they were
+// materialised in registers, twice the vector instructions.
+__device__ __forceinline__ uint64_t ring_hit(const RingSlot& r, const RingGauss& G) {
+  const float sd = fmaf(r.sh, G.cc, -(r.ch * G.sc));  // sin((lat_r - lat_c) / 2)
+  const float num = fmaf(-sd, sd, G.hrs);
+  const float den = G.clat * r.clat;
+  // y = |omega - middle| reduced to [0, pi]: sin(y / 2), cos(y / 2)
+  const float a = fabsf(fmaf(G.sw, r.cm, -(G.cw * r.sm)));
+  const float b = fabsf(fmaf(G.cw, r.cm, G.sw * r.sm));
+  const float sdist = fmaf(a, r.chw, -(b * r.shw));  // sin((y - half-width) / 2)
+  // in the disc's z range, and: the whole ring lies in the disc (also at the
+  // poles), or the disc reaches it and the centre's longitude lies in the
+  // widened interval or near enough to it
+  return __builtin_amdgcn_ballot_w64(fabsf(sd) <= G.srs) &
+         (__builtin_amdgcn_ballot_w64(num >= den) |
+          (__builtin_amdgcn_ballot_w64(num > 0.f) &
+           (__builtin_amdgcn_ballot_w64(a <= r.shw) | __builtin_amdgcn_ballot_w64(den * (sdist * sdist) < num))));
+}
+
+// What the filter reads of a Gaussian, once per Gaussian instead of once per
+// (tile, Gaussian) candidate, of which there are some 49 to one: RING 32 B
+// (RingGauss), NESTED 16 B (direction and squared chord of r_s).
+template <int MODE>
+__global__ __launch_bounds__(256) void k_query_gauss(int64_t P, const float4* __restrict__ disc,
+                                                     const float* __restrict__ radius, float4* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= P) return;
+  const float4 d = disc[i];
+  const float rs = radius[i];
+  if (MODE == HP_QUERY_NESTED) {
+    const float c = 2.f * sinf(0.5f * rs);
+    out[i] = make_float4(d.x, d.y, d.z, c * c);
+  } else {
+    const RingGauss G = ring_gauss(d, rs);
+    out[2 * i] = make_float4(G.cc, G.sc, G.sw, G.cw);
+    out[2 * i + 1] = make_float4(G.clat, G.srs, G.hrs, 0.f);
   }
-  return false;
+}
+
+// A wave filters a tile's list, kQueryIlp x 64 entries at a time (their gathers
+// in flight together); the four waves of a workgroup take four neighbouring
+// tiles, whose lists hold mostly the same Gaussians in the same order, so
+// that part of the gathers meet in the CU's cache and no barrier orders the
+// waves.  1M Gaussians on the full sphere at Nside 512, RING x 4, 49M
+// candidates: 619 us with a workgroup per tile and the trigonometry per
+// candidate, 446 us with that done once per Gaussian, 351 us with predicates as
+// wave masks and two lanes to a record.  Bound by the vector instructions of
+// the ring tests (225 us of issue) and by the gathers.
+constexpr int kQueryIlp = 4;
+
+// The 32-byte records of 64 list entries: two lanes fetch a record together,
+// one 16-byte half each (a lane per record spent two cache accesses on it, and
+// the accesses bound the kernel), and exchange halves with their neighbour.
+// Even lanes end with entry lane / 2, odd lanes with entry 32 + lane / 2.
+__device__ __forceinline__ float swap_pair(float v) { return hp_dpp<0xB1>(v); }  // lane ^ 1
+__device__ __forceinline__ RingGauss pair_load(const float4* __restrict__ gauss, uint32_t ga, uint32_t gb, bool odd) {
+  const float4 ha = gauss[2 * (int64_t)ga + (odd ? 1 : 0)], hb = gauss[2 * (int64_t)gb + (odd ? 1 : 0)];
+  const float4 t = odd ? ha : hb;
+  const float4 r = make_float4(swap_pair(t.x), swap_pair(t.y), swap_pair(t.z), 0.f);
+  const float rw = swap_pair(t.w);
+  RingGauss G;
+  G.cc = odd ? r.x : ha.x;
+  G.sc = odd ? r.y : ha.y;
+  G.sw = odd ? r.z : ha.z;
+  G.cw = odd ? rw : ha.w;
+  G.clat = odd ? hb.x : r.x;
+  G.srs = odd ? hb.y : r.y;
+  G.hrs = odd ? hb.z : r.z;
+  return G;
 }
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_query_filter(QueryArgs A) {
+__global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) {
   if (*A.n_pairs > A.capacity) return;  // the candidates were not written
-  __shared__ float4 s_pt[MODE == HP_QUERY_NESTED ? kMaxPts : 1];
-  __shared__ RingSlot s_ring[MODE == HP_QUERY_RING ? kMaxRings : 1];
-  __shared__ uint32_t s_key[kMaxRings], s_len[kMaxRings];
-  __shared__ uint32_t s_wcnt[4];
-  const int k = hp_xcd_tile((int)blockIdx.x, (int)gridDim.x);
-  const int64_t t = A.active_tiles[k];
-  const int tid = threadIdx.x;
+  __shared__ float4 s_pts[4][MODE == HP_QUERY_NESTED ? kMaxPts : 1];
+  __shared__ RingSlot s_rings[4][MODE == HP_QUERY_RING ? kMaxRings : 1];
+  __shared__ uint32_t s_keys[4][kMaxRings], s_lens[4][kMaxRings];
+  const int lane = hp_lane();
+  const int wv = (int)hp_uniform(threadIdx.x >> 6);
+  const int k = 4 * hp_xcd_tile((int)blockIdx.x, (int)gridDim.x) + wv;
+  if (k >= n_tiles) return;  // waves are independent: no barrier below
+  float4* s_pt = s_pts[wv];
+  RingSlot* s_ring = s_rings[wv];
+  uint32_t *s_key = s_keys[wv], *s_len = s_lens[wv];
+  const int t = A.active_tiles[k];
   const int f = 1 << A.fl, nsub = f * f;
   int npts = 0, nslot = 0;
   if (MODE == HP_QUERY_NESTED) {
     // centres of the nodes of orders kt .. kq below t, coarsest first
     npts = (4 * nsub - 1) / 3;
-    for (int j = tid; j < npts; j += blockDim.x) {
+    for (int j = lane; j < npts; j += 64) {
       int o = 0, base = 0;
       while (j >= base + (1 << (2 * o))) { base += 1 << (2 * o); ++o; }
       double v[3];
-      hp_pix_dir(A.order_t + o, (t << (2 * o)) + (j - base), v);
+      hp_pix_dir(A.order_t + o, ((int64_t)t << (2 * o)) + (j - base), v);
       s_pt[j] = make_float4((float)v[0], (float)v[1], (float)v[2], 0.f);
     }
   } else {
@@ -168,25 +233,25 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A) {
     hp_nest_xyf(A.order_t, t, &xt, &yt, &ft);
     const int64_t N = (int64_t)1 << A.kq;
     const int64_t ring_min = (int64_t)((ft >> 2) + 2) * N - ((int64_t)xt * f + f - 1) - ((int64_t)yt * f + f - 1) - 1;
-    if (tid < nslot) { s_key[tid] = 0xffffffffu; s_len[tid] = 0u; }
-    __syncthreads();
-    if (tid < nsub) {
+    if (lane < nslot) { s_key[lane] = 0xffffffffu; s_len[lane] = 0u; }
+    __builtin_amdgcn_wave_barrier();
+    for (int j = lane; j < nsub; j += 64) {
       int64_t ir;
       int pos, xmy;
-      pix_ring(A.kq, (t << (2 * A.fl)) + tid, &ir, &pos, &xmy);
-      const int j = (int)(ir - ring_min);
+      pix_ring(A.kq, ((int64_t)t << (2 * A.fl)) + j, &ir, &pos, &xmy);
+      const int o = (int)(ir - ring_min);
       // first pixel of the run: the smallest x - y (positions grow with it)
-      atomicMin(&s_key[j], ((uint32_t)(xmy + 16384) << 17) | (uint32_t)pos);
-      atomicAdd(&s_len[j], 1u);
+      atomicMin(&s_key[o], ((uint32_t)(xmy + 16384) << 17) | (uint32_t)pos);
+      atomicAdd(&s_len[o], 1u);
     }
-    __syncthreads();
-    if (tid < nslot) {
+    __builtin_amdgcn_wave_barrier();
+    if (lane < nslot) {
       double lat, clat;
       int nring;
       float off;
-      ring_geom(N, ring_min + tid, &lat, &clat, &nring, &off);
-      const int len = (int)s_len[tid];
-      const int start = len ? (int)(s_key[tid] & 0x1ffffu) : 0;
+      ring_geom(N, ring_min + lane, &lat, &clat, &nring, &off);
+      const int len = (int)s_len[lane];
+      const int start = len ? (int)(s_key[lane] & 0x1ffffu) : 0;
       const double step = 2.0 * M_PI / (double)nring;
       const double mid = ((double)start + 0.5 * (double)(len - 1) + (double)off) * step;
       const double hw = 0.5 * (double)(len + 1) * step;
@@ -198,50 +263,84 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A) {
       r.cm = (float)cos(0.5 * mid);
       r.shw = (float)sin(0.5 * (hw < M_PI ? hw : M_PI));
       r.chw = (float)cos(0.5 * (hw < M_PI ? hw : M_PI));
-      r.whole = len == 0 ? -1 : (hw >= M_PI ? 1 : 0);
-      s_ring[tid] = r;
+      if (hw >= M_PI) r.shw = 2.f;
+      if (len == 0) { r.sh = 4.f; r.ch = 0.f; }
+      // the middle ring first, then outwards: most candidates are decided by the
+      // first rings, and a wave stops when all of its are
+      const int out = lane - (f - 1);
+      s_ring[out > 0 ? 2 * out - 1 : -2 * out] = r;
     }
   }
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();
 
-  const uint32_t s = A.ranges[2 * k], e = A.ranges[2 * k + 1];
-  const int lane = hp_lane(), wv = tid >> 6;
+  const uint32_t s = hp_uniform(A.ranges[2 * k]), e = hp_uniform(A.ranges[2 * k + 1]);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  constexpr uint64_t kEven = 0x5555555555555555ull, kOdd = ~kEven;
+  const bool odd = (lane & 1) != 0;
   uint32_t kept = 0;
-  for (uint32_t base = s; base < e; base += blockDim.x) {
-    const uint32_t idx = base + (uint32_t)tid;
-    const bool have = idx < e;
-    const uint32_t g = have ? A.vals[idx] : 0u;
-    bool keep = false;
-    if (have) {
-      const float4 r0 = A.disc[g];
-      const float rs = A.radius[g];
-      if (MODE == HP_QUERY_NESTED) {
-        const float c = 2.f * sinf(0.5f * rs);
-        const float thr = c * c;
-        for (int j = 0; j < npts && !keep; ++j) {
-          const float4 p = s_pt[j];
-          const float dx = p.x - r0.x, dy = p.y - r0.y, dz = p.z - r0.z;
-          keep = fmaf(dz, dz, fmaf(dy, dy, dx * dx)) <= thr;
-        }
+  for (uint32_t base = s; base < e; base += kQueryIlp * 64) {
+    // RING: entry lane / 2 for the even lanes, 32 + lane / 2 for the odd ones
+    // (pair_load); NESTED: entry `lane`
+    uint32_t g[kQueryIlp], ga[kQueryIlp], gb[kQueryIlp];
+    uint64_t m[kQueryIlp], have[kQueryIlp];  // lanes kept, lanes with an entry
+#pragma unroll
+    for (int q = 0; q < kQueryIlp; ++q) {
+      if (MODE == HP_QUERY_RING) {
+        const uint32_t ia = base + 64u * q + (uint32_t)(lane >> 1), ib = ia + 32u;
+        ga[q] = ia < e ? A.vals[ia] : 0u;
+        gb[q] = ib < e ? A.vals[ib] : 0u;
+        g[q] = odd ? gb[q] : ga[q];
+        have[q] = __builtin_amdgcn_ballot_w64((odd ? ib : ia) < e);
       } else {
-        const float hs = sinf(0.5f * rs);
-        keep = ring_hit(s_ring, nslot, r0.x, r0.y, r0.z, hs * hs);
+        const uint32_t idx = base + 64u * q + (uint32_t)lane;
+        have[q] = __builtin_amdgcn_ballot_w64(idx < e);
+        g[q] = idx < e ? A.vals[idx] : 0u;
+      }
+      m[q] = 0;
+    }
+    if (MODE == HP_QUERY_NESTED) {
+      float4 d[kQueryIlp];
+#pragma unroll
+      for (int q = 0; q < kQueryIlp; ++q) d[q] = A.gauss[g[q]];
+      for (int j = 0; j < npts; ++j) {
+        const float4 p = s_pt[j];
+        uint64_t open = 0;
+#pragma unroll
+        for (int q = 0; q < kQueryIlp; ++q) {
+          const float dx = p.x - d[q].x, dy = p.y - d[q].y, dz = p.z - d[q].z;
+          m[q] |= __builtin_amdgcn_ballot_w64(fmaf(dz, dz, fmaf(dy, dy, dx * dx)) <= d[q].w);
+          open |= have[q] & ~m[q];
+        }
+        if (open == 0) break;
+      }
+    } else {
+      RingGauss G[kQueryIlp];
+#pragma unroll
+      for (int q = 0; q < kQueryIlp; ++q) G[q] = pair_load(A.gauss, ga[q], gb[q], odd);
+      for (int j = 0; j < nslot; ++j) {
+        const RingSlot r = s_ring[j];
+        uint64_t open = 0;
+#pragma unroll
+        for (int q = 0; q < kQueryIlp; ++q) {
+          m[q] |= ring_hit(r, G[q]);
+          open |= have[q] & ~m[q];
+        }
+        if (open == 0) break;
       }
     }
-    // every entry of this chunk has been read (the tests used them); the
-    // kept ones move down to the tile's next free slots, in order
-    const uint64_t m = __ballot(keep);
-    if (lane == 0) s_wcnt[wv] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t off = kept;
-    for (int w = 0; w < wv; ++w) off += s_wcnt[w];
-    const uint32_t tot = s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
-    if (keep) A.vals[s + off + (uint32_t)__popcll(m & below)] = g;
-    kept += tot;
-    __syncthreads();
+    // every entry of these has been read (the tests used them), and the next
+    // ones lie behind them: the kept ones move down to the tile's next free
+    // slots, in order
+#pragma unroll
+    for (int q = 0; q < kQueryIlp; ++q) {
+      m[q] &= have[q];
+      // kept entries before this lane's
+      const uint64_t before = MODE == HP_QUERY_RING ? (odd ? kEven | (kOdd & below) : kEven & below) : below;
+      if ((m[q] >> lane) & 1ull) A.vals[s + kept + (uint32_t)__popcll(m[q] & before)] = g[q];
+      kept += (uint32_t)__popcll(m[q]);
+    }
   }
-  if (tid == 0) {
+  if (lane == 0) {
     A.ranges[2 * k + 1] = s + kept;
     if (A.n_kept) atomicAdd(A.n_kept, (unsigned long long)kept);
   }
@@ -282,12 +381,21 @@ extern "C" hp_status hp_bin_query(int32_t phase, int32_t mode, int32_t f, const 
   if (P == 0 || n_tiles == 0) return HP_OK;
   const HpProjView pv = hp_proj_view((const char*)projected, P);
   const HpMaskView mv = hp_mask_view((const char*)mask, g);
-  QueryArgs A{mode, kq, fl, g.kt, mv.active_tiles, pv.disc, pv.radius, vals, tile_ranges, n_pairs, capacity,
-              (unsigned long long*)n_kept};
+  // in a part of the workspace that a repeated emission does not read
+  float4* gauss = (float4*)hp_bin_spare(ws, P);
+  const dim3 gg(hp_blocks(P, 256));
   if (mode == HP_QUERY_RING)
-    hipLaunchKernelGGL(k_query_filter<HP_QUERY_RING>, dim3((unsigned)n_tiles), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(k_query_gauss<HP_QUERY_RING>, gg, dim3(256), 0, s, P, pv.disc, pv.radius, gauss);
   else
-    hipLaunchKernelGGL(k_query_filter<HP_QUERY_NESTED>, dim3((unsigned)n_tiles), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(k_query_gauss<HP_QUERY_NESTED>, gg, dim3(256), 0, s, P, pv.disc, pv.radius, gauss);
+  HP_CHECK_LAUNCH();
+  QueryArgs A{mode, kq, fl, g.kt, mv.active_tiles, gauss, vals, tile_ranges, n_pairs, capacity,
+              (unsigned long long*)n_kept};
+  const dim3 wgs(hp_blocks(n_tiles, 4));
+  if (mode == HP_QUERY_RING)
+    hipLaunchKernelGGL(k_query_filter<HP_QUERY_RING>, wgs, dim3(256), 0, s, A, (int)n_tiles);
+  else
+    hipLaunchKernelGGL(k_query_filter<HP_QUERY_NESTED>, wgs, dim3(256), 0, s, A, (int)n_tiles);
   HP_CHECK_LAUNCH();
   return HP_OK;
 }
