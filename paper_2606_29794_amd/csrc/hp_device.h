@@ -313,65 +313,52 @@ __device__ __forceinline__ void hp_wave_totals(float* v) {
   }
 }
 
-// Same sums, left in lane 63 only: after the row sums, row_bcast:15 adds
-// row r-1's sum into rows 1 and 3, and row_bcast:31 adds lane 31 (rows 0+1)
-// into rows 2 and 3, so lane 63 ends with the total of the wave.
-template <int N>
-__device__ __forceinline__ void hp_wave_totals_lane63(float* v) {
-#pragma unroll
-  for (int m = 0; m < N; ++m) v[m] += hp_dpp<0xB1>(v[m]);
-#pragma unroll
-  for (int m = 0; m < N; ++m) v[m] += hp_dpp<0x4E>(v[m]);
-#pragma unroll
-  for (int m = 0; m < N; ++m) v[m] += hp_dpp<0x141>(v[m]);
-#pragma unroll
-  for (int m = 0; m < N; ++m) v[m] += hp_dpp<0x140>(v[m]);
-#pragma unroll
-  for (int m = 0; m < N; ++m)
-    v[m] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[m]), 0x142, 0xa, 0xf, false));
-#pragma unroll
-  for (int m = 0; m < N; ++m)
-    v[m] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[m]), 0x143, 0xc, 0xf, false));
+// Nine sums over the 64 lanes (all active) at once by recursive halving.  Inside
+// a row of 16 lanes DPP adds whose bank mask writes only half of the lanes merge
+// two values into one register, two instructions per pair and step; the rows
+// are joined last, when two registers are left (a permlane swap takes two
+// issue slots: joining the rows first, as gfx950's swaps also allow, took 36
+// slots, this takes 25).  Returns, in lane L < 32, the total of value
+// 4 (L bit 3) + 2 (L bit 2) + (L bit 4), and in every lane of the last row that
+// of the ninth value.  The adds are in asm because the compiler does not form
+// masked DPP adds; every register is written at least two instructions before
+// a DPP operand reads it, as the hardware asks, and the s_nop cover the
+// neighbours.
+__device__ __forceinline__ float hp_wave_totals9(float* v) {
+#define HP_RS_LO(x) "v_add_f32_dpp " x ", " x ", " x " row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+#define HP_RS_HI(x, y) "v_add_f32_dpp " x ", " y ", " y " row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+#define HP_RS_EVEN(x) "v_add_f32_dpp " x ", " x ", " x " row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+#define HP_RS_ODD(x, y) "v_add_f32_dpp " x ", " y ", " y " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+#define HP_RS_ALL(x, ctrl) "v_add_f32_dpp " x ", " x ", " x " " ctrl " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t"
+      // lanes with bit 3 clear keep values 0..3, the others take 4..7
+      HP_RS_LO("%0") HP_RS_LO("%1") HP_RS_LO("%2") HP_RS_LO("%3") HP_RS_ALL("%4", "row_ror:8")
+      HP_RS_HI("%0", "%5") HP_RS_HI("%1", "%6") HP_RS_HI("%2", "%7") HP_RS_HI("%3", "%8")
+      // lanes with bit 2 clear keep %0 and %1, the others take %2 and %3
+      HP_RS_ALL("%4", "row_half_mirror") HP_RS_EVEN("%0") HP_RS_EVEN("%1")
+      HP_RS_ALL("%4", "quad_perm:[1,0,3,2]") HP_RS_ODD("%0", "%2") HP_RS_ODD("%1", "%3")
+      HP_RS_ALL("%4", "quad_perm:[2,3,0,1]") "s_nop 1"
+      : "+&v"(v[0]), "+&v"(v[1]), "+&v"(v[2]), "+&v"(v[3]), "+&v"(v[8])
+      : "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+#undef HP_RS_LO
+#undef HP_RS_HI
+#undef HP_RS_EVEN
+#undef HP_RS_ODD
+#undef HP_RS_ALL
+  // even rows keep %0, odd rows take %1
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[0]), __float_as_uint(v[1]), false, false);
+  float x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  x += hp_dpp<0xB1>(x);
+  x += hp_dpp<0x4E>(x);
+  // the halves of x in lanes 0..31, those of the ninth value in lanes 32..63
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(v[8]), false, false);
+  float w = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0x8 bank_mask:0xf" : "+v"(w));
+  return w;
 }
 
-// Eight sums over the 64 lanes at once by recursive halving: every exchange
-// step moves half of the remaining values to the partner lane group, so the
-// 8 x 64 inputs need 4 + 2 + 1 cross-lane moves plus three butterfly adds
-// instead of 8 x 6.  gfx950's permlane32 swap pairs lane L with L ^ 32 and
-// permlane16 swap pairs L with L ^ 16; a row rotation by 8 pairs L with L ^ 8.
-// On return, lane L holds the total of value L >> 3 in all eight lanes of its
-// group (L & ~7 .. L | 7).
-__device__ __forceinline__ float hp_wave_totals8_spread(const float* v) {
-  float w[4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    // low half keeps value m, high half keeps value m + 4
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[m]), __float_as_uint(v[m + 4]), false, false);
-    w[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  float x[2];
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    // even rows keep w[m], odd rows keep w[m + 2]
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[m]), __float_as_uint(w[m + 2]), false, false);
-    x[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  // lanes with bit 3 clear keep x[0] and take x[0] of lane L ^ 8; the others
-  // keep x[1] and take x[1] of lane L ^ 8
-  const bool hi = (hp_lane() & 8) != 0;
-  const float send = hi ? x[0] : x[1];
-  const float keep = hi ? x[1] : x[0];
-  float y = keep + hp_dpp<0x128>(send);  // row_ror:8
-  y += hp_dpp<0xB1>(y);
-  y += hp_dpp<0x4E>(y);
-  y += hp_dpp<0x141>(y);
-  return y;
-}
-
-// A ninth sum beside hp_wave_totals8_spread: the same exchanges applied to
-// one value alone (each swap pairs the value with itself), so every lane ends
-// with the wave's total.
-__device__ __forceinline__ float hp_wave_total_all(float z) {
+// The sum over the 64 lanes in every lane (each swap pairs the value with itself).
+__device__ __forceinline__ float hp_wave_sum_dpp(float z) {
   {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
     z = __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -387,11 +374,20 @@ __device__ __forceinline__ float hp_wave_total_all(float z) {
   return z;
 }
 
-__device__ __forceinline__ float hp_wave_sum(float v) {
-  // butterfly over 64 lanes with cross-lane shuffles
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+// The same for the largest of 64 values; fmaxf passes over a NaN.
+__device__ __forceinline__ float hp_wave_max_dpp(float z) {
+  {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+    z = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+    z = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  z = fmaxf(z, hp_dpp<0x128>(z));
+  z = fmaxf(z, hp_dpp<0xB1>(z));
+  z = fmaxf(z, hp_dpp<0x4E>(z));
+  return fmaxf(z, hp_dpp<0x141>(z));
 }
 
 __device__ __forceinline__ uint32_t hp_wave_prefix_u32(uint32_t v, uint32_t* total) {

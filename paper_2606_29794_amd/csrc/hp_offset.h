@@ -52,7 +52,7 @@ __device__ __forceinline__ float hp_k2_series(float s2) {
   return 1.f + s2 * (0.33333333f + s2 * (0.17777778f + s2 * (0.11428571f + s2 * (0.081269841f + s2 * 0.061568062f))));
 }
 __device__ __forceinline__ float hp_k2_series_deriv(float s2) {  // d k2 / d s2
-  return 0.33333333f + s2 * (2.f * 0.17777778f + s2 * (3.f * 0.11428571f + s2 * (4.f * 0.081269841f + s2 * 5.f * 0.061568062f)));
+  return 0.33333333f + s2 * (2.f * 0.17777778f + s2 * (3.f * 0.11428571f + s2 * (4.f * 0.081269841f + s2 * (5.f * 0.061568062f))));
 }
 
 // atan2(s, c) for s > 0 (angles in (0, pi)): reduced to t = min / max of

@@ -94,21 +94,20 @@ struct WaveCap {
 };
 __device__ __forceinline__ WaveCap wave_cap(bool valid, const float p[3]) {
   WaveCap w;
-  const float sx = hp_wave_sum(valid ? p[0] : 0.f), sy = hp_wave_sum(valid ? p[1] : 0.f),
-              sz = hp_wave_sum(valid ? p[2] : 0.f);
+  const float sx = hp_wave_sum_dpp(valid ? p[0] : 0.f), sy = hp_wave_sum_dpp(valid ? p[1] : 0.f),
+              sz = hp_wave_sum_dpp(valid ? p[2] : 0.f);
   const float inv = rsqrtf(sx * sx + sy * sy + sz * sz);  // no valid pixel: NaN centre, no entry passes
   w.cx = sx * inv; w.cy = sy * inv; w.cz = sz * inv;
   const float dx = p[0] - w.cx, dy = p[1] - w.cy, dz = p[2] - w.cz;
   float c2 = valid ? dx * dx + dy * dy + dz * dz : 0.f;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) c2 = fmaxf(c2, __shfl_xor(c2, off, 64));
+  c2 = hp_wave_max_dpp(c2);
   w.sr = fminf(1.f, 0.5f * sqrtf(c2) * 1.0001f + 1e-6f);  // sin(R/2) = chord / 2
   w.cr = sqrtf(fmaxf(0.f, 1.f - w.sr * w.sr));
   return w;
 }
 // entry with unit direction u and sg = sin((r_s + guard) / 2) (record word 15)
 __device__ __forceinline__ bool wave_cap_hit(const WaveCap& w, float4 r0, float sg) {
-  const float cg = sqrtf(fmaxf(0.f, 1.f - sg * sg));
+  const float cg = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - sg * sg));
   const float dx = w.cx - r0.x, dy = w.cy - r0.y, dz = w.cz - r0.z;
   const float sh = w.sr * cg + w.cr * sg;  // sin((R + theta) / 2)
   const float ch = w.cr * cg - w.sr * sg;  // cos((R + theta) / 2)
@@ -126,8 +125,8 @@ __device__ __forceinline__ bool wave_ellipse_hit(const WaveCap& w, float4 r1, fl
   const float wp[3] = {w.cx, w.cy, w.cz};
   const HpOffset o = hp_offset(wp, r1, r2);
   const float h = 0.5f * (r2.y - r2.w);
-  const float lmax = 0.5f * (r2.y + r2.w) + sqrtf(h * h + r2.z * r2.z);
-  const float lim = rq_cut + 2.f * w.sr * sqrtf(fmaxf(lmax, 0.f));
+  const float lmax = 0.5f * (r2.y + r2.w) + __builtin_amdgcn_sqrtf(h * h + r2.z * r2.z);
+  const float lim = rq_cut + 2.f * w.sr * __builtin_amdgcn_sqrtf(fmaxf(lmax, 0.f));
   return o.qt <= lim * lim * 1.0001f + 1e-6f;
 }
 
@@ -270,13 +269,20 @@ __global__ __launch_bounds__(256) void k_render_fwd_batch(RenderBatch B) {
 // [0..2] colour, [3] opacity, [4..6] conic (A, B, C), [7] omega, [8] phi,
 // [9] inverse radial depth 1/r (written only with a depth gradient).
 #define HP_NACC 10
-// constant factor of each value as the per-pixel terms leave it out
-__constant__ float kFlushScale[HP_NACC] = {1.f, 1.f, 1.f, 1.f, -0.5f, -1.f, -0.5f, -1.f, -1.f, 1.f};
 template <bool B>
 struct HpBool {
   static constexpr bool value = B;
 };
 
+// Bound by instruction issue: on a full sphere of order 9 with 1 M Gaussians the matrix and
+// memory pipes idle while each (wave, entry) visit issues about 90 vector
+// instructions, a quarter of them for the sums over the wave.  What a visit
+// can leave to the Gaussian is left to the flush, which runs once per (block,
+// entry): constant factors and the sin(phi) part of dL/domega, which is a
+// combination of the conic's totals; lanes without a hit take part with alpha =
+// 0, which needs no further selects.  With these and hp_wave_totals9: 862 ->
+// 773 us (full sphere of order 9, 1 M Gaussians), 314 -> 282 us (pinhole of 75
+// degrees with depth, order 10).
 // DEPTH: the upstream gradient also holds dL/d(inverse depth) per pixel; the
 // inverse depth enters the compositing like a colour channel, and the tenth
 // accumulator receives dL/d(1/r) per Gaussian.
@@ -316,6 +322,9 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
   for (int off = 32; off >= 1; off >>= 1) ncmax = max(ncmax, __shfl_xor(ncmax, off, 64));
   ncmax = (int)hp_uniform((uint32_t)ncmax);
   const int tid = threadIdx.x, lane = hp_lane();
+  // the total that hp_wave_totals9 leaves in this lane, and whether it sends it
+  float* const s_mine = s_acc + (lane < 32 ? ((lane >> 1) & 6) | ((lane >> 4) & 1) : lane - 40);
+  const bool sends = (lane < 32 && (lane & 3) == 0) || lane == 48 || (DEPTH && lane == 49);
   const WaveCap wc = wave_cap(valid, p);
   const float rq_cut = sqrtf(A.q_cut);
   if (lane == 0) s_nc[tid >> 6] = ncmax;
@@ -403,11 +412,11 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
         const float G = hp_exp_neg_half(q);
         const float oG = r0.w * G;
         const bool lin = oG < amax;  // below the clamp alpha depends on q and opacity
-        const float alpha = lin ? oG : amax;
+        const float alpha = hit ? fminf(oG, amax) : 0.f;
         const float iom = __builtin_amdgcn_rcpf(1.f - alpha);
-        const float Tb = Tcur * iom;  // transmittance before this entry
-        const float wgt = hit ? alpha * Tb : 0.f;
-        float v[NA];
+        const float Tb = Tcur * iom;  // transmittance before this entry (iom = 1 without a hit)
+        const float wgt = alpha * Tb;
+        float v[9];
         v[0] = g0 * wgt;
         v[1] = g1 * wgt;
         v[2] = g2 * wgt;
@@ -416,10 +425,10 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
         if (DEPTH) gr += gD * curd[i];
         const float dLda = (hit && lin) ? Tb * gr - iom * SgT : 0.f;
         SgT += wgt * gr;
-        Tcur = hit ? Tb : Tcur;
+        Tcur = Tb;
         v[3] = dLda * G;
         // m = -2 dL/dq; values 4..8 leave out their constant factors, which
-        // the flush applies once per Gaussian (kFlushScale)
+        // the flush applies once per Gaussian
         const float m = alpha * dLda;
         const float mk = m * k2h;
         const float ma = mk * a, mb = mk * b;
@@ -433,31 +442,23 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
         // motion of (a, b, c) with the Gaussian's longitude / latitude:
         // da/dw = -cos(phi) c + sin(phi) b, db/dw = -sin(phi) a, dc/dw = cos(phi) a
         // da/dp = 0, db/dp = -c, dc/dp = b
-        const float cph = r1.w, sph = r0.y;
-        float t2, t3;
+        // Here only the part of c and hc; the part of sin(phi) is the entry's
+        // combination of values 4..6 (flush)
+        const float mc = m * c;
         if constexpr (FAR) {
-          const float hc = 0.5f * qt * d2;
-          t2 = hc * a - fa * c;
-          t3 = hc * b - fb * c;
+          const float mh = m * (0.5f * qt * d2);
+          v[7] = mc * fa - mh * a;
+          v[8] = mc * fb - mh * b;  // dL/dphi = v8
         } else {
-          t2 = -(fa * c);
-          t3 = -(fb * c);
+          v[7] = mc * fa;
+          v[8] = mc * fb;
         }
-        v[7] = m * (sph * (fa * b - fb * a) + cph * t2);  // dL/domega = -v7
-        v[8] = m * t3;                                     // dL/dphi = -v8
-        if constexpr (DEPTH) v[9] = gD * wgt;              // dL/d(1/r)
-        // values 0..7: lane 8m holds the wave's total of value m; value 8: every lane
-        const float t8 = hp_wave_totals8_spread(v);
-        const float t9 = hp_wave_total_all(v[8]);
+        float total = hp_wave_totals9(v);
         if constexpr (DEPTH) {
-          const float t10 = hp_wave_total_all(v[9]);
-          if ((lane & 7) == 0 || lane == 1 || lane == 2)
-            atomicAdd(&s_acc[i * NA + (lane == 1 ? 8 : (lane == 2 ? 9 : lane >> 3))],
-                      lane == 1 ? t9 : (lane == 2 ? t10 : t8));
-        } else {
-          if ((lane & 7) == 0 || lane == 1)
-            atomicAdd(&s_acc[i * NA + (lane == 1 ? 8 : lane >> 3)], lane == 1 ? t9 : t8);
+          const float t10 = hp_wave_sum_dpp(gD * wgt);  // dL/d(1/r)
+          total = lane == 49 ? t10 : total;
         }
+        if (sends) atomicAdd(s_mine + i * NA, total);
       };
       if (((__builtin_amdgcn_ballot_w64(!(c > 0.f)) | __builtin_amdgcn_ballot_w64(!(s2 < HP_K2_S2MAX))) & m1) == 0)
         composite(HpBool<false>{});
@@ -468,14 +469,43 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
     if (qs == 3) s_gid[(ctop - ch + 1) & 1][e] = gstage;
     if (DEPTH && qs == 2) s_invd[(ctop - ch + 1) & 1][e] = 1.f / dstage;
     __syncthreads();  // the chunk's totals are complete and the next chunk is staged
-    for (int t = tid; t < HP_CHUNK * NA; t += 256) {
-      const float x = s_acc[t];
-      if (x != 0.f) {
-        const int i = t / NA, m = t - i * NA;
-        const uint32_t g = s_gid[(ctop - ch) & 1][i];
-        unsafeAtomicAdd(&acc[(int64_t)m * P + g], x * kFlushScale[m]);
-        s_acc[t] = 0.f;
+    // Four threads of a wave per entry send its non-zero totals and clear them
+    // (each thread's reads come before any of the wave's writes): thread qs = 0
+    // the colours, 1 opacity, dL/dphi and the inverse depth, 2 the conic, 3
+    // dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa
+    // - hc a); the first sum is (A - C) S5 + B (S6 - S4) in the totals S4..S6
+    {
+      float* S = s_acc + e * NA;
+      const uint32_t g = s_gid[(ctop - ch) & 1][e];
+      float x0, x1 = 0.f, x2 = 0.f;
+      int m0, m1 = 0, m2 = 0;
+      if (qs == 0) {
+        x0 = S[0]; x1 = S[1]; x2 = S[2];
+        m0 = 0; m1 = 1; m2 = 2;
+      } else if (qs == 1) {
+        x0 = S[3]; x1 = S[8];
+        m0 = 3; m1 = 8;
+        if constexpr (DEPTH) { x2 = S[9]; m2 = 9; }
+      } else {
+        x0 = S[4]; x1 = S[5]; x2 = S[6];
+        m0 = 4; m1 = 5; m2 = 6;
       }
+      if (qs == 3) {
+        const float4 r2 = cur[4 * e + 2];
+        x0 = cur[4 * e + 1].w * S[7] - cur[4 * e].y * ((r2.y - r2.w) * x1 + r2.z * (x2 - x0));
+        x1 = x2 = 0.f;
+        m0 = 7;
+      }
+      if (qs == 2) {  // constant factors of the conic's values
+        x0 *= -0.5f;
+        x1 = -x1;
+        x2 *= -0.5f;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (x0 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m0 * P + g], x0);
+      if (x1 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m1 * P + g], x1);
+      if (x2 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m2 * P + g], x2);
+      for (int m = qs; m < NA; m += 4) S[m] = 0.f;
     }
     __syncthreads();  // totals sent and cleared before the next chunk adds to them
   }
