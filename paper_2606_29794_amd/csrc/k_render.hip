@@ -95,6 +95,7 @@ __device__ __forceinline__ float4 stage_load(const float4* __restrict__ rec, uin
 __device__ __forceinline__ float uniform_f32(float v) { return __uint_as_float(hp_uniform(__float_as_uint(v))); }
 struct WaveCap {
   float cx, cy, cz, sr, cr;
+  float near2;  // squared chord from the centre below which every pixel is near an entry
 };
 __device__ __forceinline__ WaveCap wave_cap(bool valid, const float p[3]) {
   WaveCap w;
@@ -109,15 +110,25 @@ __device__ __forceinline__ WaveCap wave_cap(bool valid, const float p[3]) {
   c2 = hp_wave_max_dpp(c2);
   w.sr = uniform_f32(fminf(1.f, 0.5f * sqrtf(c2) * 1.0001f + 1e-6f));  // sin(R/2) = chord / 2
   w.cr = uniform_f32(sqrtf(fmaxf(0.f, 1.f - w.sr * w.sr)));
+  // Every pixel is within the chord 2 sr of the centre: an entry within 0.24 -
+  // 2 sr of it is within 0.24 of them all, which is s^2 < 0.0576 and c > 0.97,
+  // inside the range of the k2 series (HP_K2_S2MAX = 0.0625) by a margin far
+  // above the rounding of u, of the centre and of s^2.
+  const float nr = 0.24f - 2.f * w.sr;
+  w.near2 = uniform_f32(nr > 0.f ? nr * nr : -1.f);
   return w;
 }
-// entry with unit direction u and sg = sin((r_s + guard) / 2) (record word 15)
-__device__ __forceinline__ bool wave_cap_hit(const WaveCap& w, float4 r0, float sg) {
-  const float cg = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - sg * sg));
+// squared chord from the wave's centre to an entry's unit direction u
+__device__ __forceinline__ float wave_cap_d2(const WaveCap& w, float4 r0) {
   const float dx = w.cx - r0.x, dy = w.cy - r0.y, dz = w.cz - r0.z;
+  return dx * dx + dy * dy + dz * dz;
+}
+// entry at the squared chord d2 with sg = sin((r_s + guard) / 2) (record word 15)
+__device__ __forceinline__ bool wave_cap_hit(const WaveCap& w, float d2, float sg) {
+  const float cg = __builtin_amdgcn_sqrtf(fmaxf(0.f, 1.f - sg * sg));
   const float sh = w.sr * cg + w.cr * sg;  // sin((R + theta) / 2)
   const float ch = w.cr * cg - w.sr * sg;  // cos((R + theta) / 2)
-  return (ch <= 0.f) || (dx * dx + dy * dy + dz * dz <= 4.f * sh * sh);
+  return (ch <= 0.f) || (d2 <= 4.f * sh * sh);
 }
 
 // Second per-wave test, on the 3-sigma ellipse instead of the r_s disc:
@@ -148,7 +159,7 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& A, const Rende
   const uint32_t j0 = hp_uniform(A.ranges[2 * ct]), j1 = hp_uniform(A.ranges[2 * ct + 1]);
   const uint32_t n = j1 - j0;
   float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Dinv = 0.f;
-  bool done = !valid;
+  uint64_t live = __builtin_amdgcn_ballot_w64(valid);  // pixels that still composite
   uint32_t used = n;
   int nu = 0;
   const int tid = threadIdx.x;
@@ -183,46 +194,47 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& A, const Rende
     const float4* cur = s_rec + (c & 1) * HP_STAGE;
     const float* curd = s_invd + (c & 1) * HP_CHUNK;
     const uint32_t cnt = n - base < HP_CHUNK ? n - base : HP_CHUNK;
-    // entry i: Mahalanobis bound first (q >= qt), then the exact q and the
-    // compositing step; entries go two at a time so that the second one's
-    // loads and bound overlap the first one's work.  Entries the wave skips
-    // have qt > q_cut at every pixel of the wave, so skipping them changes
-    // nothing; n_contrib still counts list positions.
-    auto step = [&](uint32_t i, const HpOffset& o) {
-      if (done || !(o.qt <= A.q_cut)) return;
-      const float4 r0 = cur[4 * i], r3 = cur[4 * i + 3];
-      const float qq = o.qt * hp_k2(hp_offset_s2(o), hp_offset_c(p, r0));
-      if (!(qq <= A.q_cut)) return;
-      const float alpha = fminf(A.alpha_max, r0.w * hp_exp_neg_half(qq));
-      const float w = alpha * T;
-      C0 += w * r3.x;
-      C1 += w * r3.y;
-      C2 += w * r3.z;
-      if (DEPTH) Dinv += w * curd[i];
-      T -= w;
-      ++nu;
-      if (T < A.eps_T) {
-        done = true;
-        used = base + i + 1;
-      }
-    };
     // only entries that can reach a pixel of this wave (lane j tests entry j
-    // against the wave's cap and ellipse bound), front to back
-    uint64_t todo = __ballot((uint32_t)lane < cnt && wave_cap_hit(wc, cur[4 * lane], cur[4 * lane + 3].w) &&
+    // against the wave's cap and ellipse bound), front to back.  The entries
+    // skipped have qt > q_cut at every pixel of the wave, so skipping them
+    // changes nothing; n_contrib still counts list positions.
+    const float d2 = wave_cap_d2(wc, cur[4 * lane]);
+    uint64_t todo = __ballot((uint32_t)lane < cnt && wave_cap_hit(wc, d2, cur[4 * lane + 3].w) &&
                              wave_ellipse_hit(wc, cur[4 * lane + 1], cur[4 * lane + 2], rq_cut));
-    while (todo != 0) {
-      if (__ballot(!done) == 0) break;
-      const uint32_t ia = (uint32_t)__builtin_ctzll(todo);
+    const uint64_t near = __builtin_amdgcn_ballot_w64(d2 <= wc.near2);
+    // Lane predicates are wave masks (scalar registers), all lanes evaluate, and
+    // only the update of the hit lanes' sums is under a mask, so that a colour
+    // that is not finite reaches no other pixel.  Bound by instruction issue,
+    // about 37 vector instructions per (wave, entry) for near entries; as nested
+    // branches with a flag per lane the copies at their ends made it 67 (full
+    // sphere of order 9, 1 M Gaussians: 411 -> 341 us; fisheye of order 8: 75 ->
+    // 63 us; pinhole of order 10 with depth: 142 -> 118 us)
+    while (todo != 0 && live != 0) {
+      const uint32_t i = (uint32_t)__builtin_ctzll(todo);
       todo &= todo - 1;
-      const HpOffset oa = hp_offset(p, cur[4 * ia + 1], cur[4 * ia + 2]);
-      if (todo != 0) {
-        const uint32_t ib = (uint32_t)__builtin_ctzll(todo);
-        todo &= todo - 1;
-        const HpOffset ob = hp_offset(p, cur[4 * ib + 1], cur[4 * ib + 2]);
-        step(ia, oa);
-        step(ib, ob);
-      } else {
-        step(ia, oa);
+      // Mahalanobis bound first (q >= qt), then the exact q
+      const HpOffset o = hp_offset(p, cur[4 * i + 1], cur[4 * i + 2]);
+      const uint64_t m1 = live & __builtin_amdgcn_ballot_w64(o.qt <= A.q_cut);
+      if (m1 == 0) continue;
+      const float4 r0 = cur[4 * i], r3 = cur[4 * i + 3];
+      const float s2 = hp_offset_s2(o);
+      const float k2 = near >> i & 1 ? hp_k2_series(s2) : hp_k2(s2, hp_offset_c(p, r0));
+      const float qq = o.qt * k2;
+      const uint64_t mh = m1 & __builtin_amdgcn_ballot_w64(qq <= A.q_cut);
+      if (__builtin_amdgcn_inverse_ballot_w64(mh)) {
+        const float alpha = fminf(A.alpha_max, r0.w * hp_exp_neg_half(qq));
+        const float w = alpha * T;
+        C0 = fmaf(w, r3.x, C0);
+        C1 = fmaf(w, r3.y, C1);
+        C2 = fmaf(w, r3.z, C2);
+        if (DEPTH) Dinv = fmaf(w, curd[i], Dinv);
+        T = fmaf(-alpha, T, T);
+        ++nu;
+      }
+      const uint64_t full = mh & __builtin_amdgcn_ballot_w64(T < A.eps_T);
+      if (full != 0) {
+        live &= ~full;
+        if (__builtin_amdgcn_inverse_ballot_w64(full)) used = base + i + 1;
       }
     }
     // one barrier both publishes the next chunk and tells whether any pixel
@@ -230,7 +242,6 @@ __device__ __forceinline__ void render_fwd_tile(const RenderArgs& A, const Rende
     s_rec[((c + 1) & 1) * HP_STAGE + tid] = stage;
     if (DEPTH && q == 0) s_invd[((c + 1) & 1) * HP_CHUNK + e] = 1.f / dstage;
     const int par = c & 1;
-    const uint64_t live = __ballot(!done);  // all lanes vote, before one lane writes
     if (lane == 0) s_live[par][tid >> 6] = live != 0;
     __syncthreads();
     if (!(s_live[par][0] | s_live[par][1] | s_live[par][2] | s_live[par][3])) break;
@@ -375,7 +386,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
     // lane j tests entry kbase + j against the wave's cap and ellipse bound; walk the hits from the back
     uint64_t todo = 0;
     if (ktop >= kbase)
-      todo = __ballot(lane <= ktop - kbase && wave_cap_hit(wc, cur[4 * lane], cur[4 * lane + 3].w) &&
+      todo = __ballot(lane <= ktop - kbase && wave_cap_hit(wc, wave_cap_d2(wc, cur[4 * lane]), cur[4 * lane + 3].w) &&
                       wave_ellipse_hit(wc, cur[4 * lane + 1], cur[4 * lane + 2], rq_cut));
     while (todo != 0) {
       const int i = 63 - __builtin_clzll(todo);
