@@ -13,7 +13,7 @@
 // cap weighs its neighbours by great-circle distance instead,
 // exp(-d^2 / (2 sigma^2 Omega)), Omega = 4 pi / Npix, which is not separable:
 // tiles holding such pixels take a direct 121-tap path with the pixel-centre
-// directions in LDS.
+// directions in LDS (from order 8 on two pixels per thread, ss_pair_rows).
 //
 // The backward pass is the transposed window: the chart neighbourhood
 // relation is symmetric with equal offset lengths, so the adjoint gathers the
@@ -42,6 +42,8 @@ struct SsimArgs {
   float g[SS_W];   // chart window taps exp(-a^2 / (2 sigma^2)), a = -5..5
   float gsum;      // their sum, accumulated in the order of the passes
   double wscale;   // 1 / (2 sigma^2 Omega): polar windows are exp(-d^2 wscale)
+  double w2[3];    // the same in base 2 as a series in s^2 = |u - v|^2 / 4 (ss_polar_weight)
+  bool fine;       // small windows: the polar weights are ss_polar_weight
   const int32_t* tables;  // [n_tiles][H*H] patch slots (see k_ssim_tables)
 };
 
@@ -119,6 +121,45 @@ __device__ __forceinline__ double ss_dist2(const double* u, const double* v) {
   return d * d;
 }
 
+// Polar window weight exp(-d^2 wscale) of a cell in direction v at the pixel in
+// direction u, h = -u / 2, where A.fine: s^2 = |u - v|^2 / 4 = 1/2 - u.v / 2 as three
+// fused multiply-adds, then the exponent to base 2 with the series of ss_dist2
+// cut after s^4; 11 vector instructions instead of 27.  From order 8 on a window
+// reaches ten steps between neighbouring centres, each under 1.6 / nside: s^2 <
+// 1e-3, where the terms left out are under 1.2e-10 of the sum.  The rounding of s^2,
+// under 5e-16, has to move the exponent by less than half a float ulp of 1: true
+// of sigma = 1.5 at every order (4.5e-9 at order 12), not of a window far
+// narrower than a pixel, which takes the general path.
+constexpr int kSsFineOrder = 8;
+__device__ __forceinline__ float ss_polar_weight(const SsimArgs& A, const double* h, double vx, double vy, double vz) {
+  const double s2 = fma(h[0], vx, fma(h[1], vy, fma(h[2], vz, 0.5)));
+  return __builtin_amdgcn_exp2f((float)(s2 * fma(s2, fma(s2, A.w2[2], A.w2[1]), A.w2[0])));
+}
+
+// Items of the direct path on tiles of 16 x 16: thread t of each half of the
+// workgroup has the pixels (t % 16, 2 (t / 16)) and the one below, so a cell of
+// their windows is read from LDS once for both.  The first half takes the first
+// six of the twelve cell rows, the second half the others; of them the first
+// row belongs to the upper pixel alone, the last one to the lower.  Bound by
+// vector instructions (about 37 per pixel and tap forward, 25 backward), the
+// columns as a real loop: unrolled, the loads gathered in front took 168
+// registers (245 and 195 us).  Fisheye of 200 degrees at order 9, 1.8 M pixels:
+// forward 335 -> 188 us, backward 391 -> 175 us against one thread per pixel
+// with the general distance.
+//   row(b, up, low): cell row b with the upper (window row b) and the lower
+//   pixel (window row b - 1) as the compile-time flags say
+template <bool B>
+struct SsBool {
+  static constexpr bool value = B;
+};
+template <class Row>
+__device__ __forceinline__ void ss_pair_rows(int half, Row row) {
+  if (half == 0) row(0, SsBool<true>{}, SsBool<false>{});
+#pragma unroll 1
+  for (int b = half == 0 ? 1 : 6, e = b + 5; b < e; ++b) row(b, SsBool<true>{}, SsBool<true>{});
+  if (half != 0) row(SS_W, SsBool<false>{}, SsBool<true>{});
+}
+
 // SSIM of one pixel and channel from its normalised window moments, and the
 // partials of the backward: d SSIM / d (sum x, sum x^2, sum xy) / Z
 __device__ __forceinline__ float ss_index(float C1, float C2, float iZ, float Sx, float Sy, float Sxx, float Syy,
@@ -168,7 +209,7 @@ struct SsFwdLds {
   float in[7][H][HP];
   union {
     float p1[16][P1S];
-    double dir[H * H][3];
+    double dir[3][H * H];
   };
 };
 
@@ -176,7 +217,7 @@ struct SsFwdLds {
 // and |img - ref|; optionally the per-pixel partials needed by the backward,
 // G[m][n] = (d SSIM / d S_m) / Z for m in (sum x, sum x^2, sum xy) x channel.
 template <int B, bool ZONES>
-__global__ __launch_bounds__(256) void k_ssim_fwd(SsimArgs A, const float* __restrict__ img,
+__global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_fwd(SsimArgs A, const float* __restrict__ img,
                                                   const float* __restrict__ ref, float* __restrict__ smap,
                                                   float* __restrict__ G, float2* __restrict__ part, int n_tiles) {
   using L = SsFwdLds<B>;
@@ -241,9 +282,9 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(SsimArgs A, const float* __res
           const int64_t q = hp_chart_pixel(A.order, f, x0 + cx - SS_R, y0 + cy - SS_R);
           double d[3] = {0.0, 0.0, 0.0};
           if (q >= 0) hp_pix_dir(A.order, q, d);
-          s.dir[cy * H + cx][0] = d[0];
-          s.dir[cy * H + cx][1] = d[1];
-          s.dir[cy * H + cx][2] = d[2];
+          s.dir[0][cy * H + cx] = d[0];
+          s.dir[1][cy * H + cx] = d[1];
+          s.dir[2][cy * H + cx] = d[2];
         }
       }
     }
@@ -347,7 +388,76 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(SsimArgs A, const float* __res
         if (full) Sm[0] = A.gsum * A.gsum;
       }
     }
-    if (direct) {
+    const bool paired = B == 16 && ZONES && direct && A.fine;
+    if constexpr (B == 16 && ZONES) if (paired) {
+      const int half = (int)hp_uniform((uint32_t)tid >> 7);
+      const int x = tid & 15, yp = 2 * ((tid & 127) >> 4);
+      const bool pol[2] = {ss_polar(A.order, hp_xyf_nest(A.order, x0 + x, y0 + yp, f)),
+                           ss_polar(A.order, hp_xyf_nest(A.order, x0 + x, y0 + yp + 1, f))};
+      const bool pure = __builtin_amdgcn_ballot_w64(!pol[0] || !pol[1]) == 0;
+      double h[2][3];
+  #pragma unroll
+      for (int j = 0; j < 2; ++j)
+  #pragma unroll
+        for (int c = 0; c < 3; ++c) h[j][c] = -0.5 * s.dir[c][(yp + j + SS_R) * H + x + SS_R];
+      float P[2][16];
+  #pragma unroll
+      for (int k = 0; k < 16; ++k) P[0][k] = P[1][k] = 0.f;
+      auto rows = [&](auto pure_tag) {
+        ss_pair_rows(half, [&](int b, auto up, auto low) {
+          constexpr bool on[2] = {decltype(up)::value, decltype(low)::value};
+          const int cell = (yp + b) * H + x, at = (yp + b) * L::HP + x;
+          const float* in = &s.in[0][0][0] + at;
+  #pragma unroll 1
+          for (int a = 0; a < SS_W; ++a) {
+            const double vx = s.dir[0][cell + a], vy = s.dir[1][cell + a], vz = s.dir[2][cell + a];
+            float m, xv[3], yv[3], xx[3], yy[3], xy[3];
+            m = in[a];
+  #pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+              xv[ch] = in[(1 + ch) * H * L::HP + a];
+              yv[ch] = in[(4 + ch) * H * L::HP + a];
+              xx[ch] = xv[ch] * xv[ch];
+              yy[ch] = yv[ch] * yv[ch];
+              xy[ch] = xv[ch] * yv[ch];
+            }
+  #pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              if (!on[j]) continue;
+              float w = ss_polar_weight(A, h[j], vx, vy, vz);
+              if constexpr (!decltype(pure_tag)::value) w = pol[j] ? w : A.g[a] * A.g[b - j];
+              P[j][0] = fmaf(w, m, P[j][0]);
+  #pragma unroll
+              for (int ch = 0; ch < 3; ++ch) {
+                P[j][1 + ch] = fmaf(w, xv[ch], P[j][1 + ch]);
+                P[j][4 + ch] = fmaf(w, yv[ch], P[j][4 + ch]);
+                P[j][7 + ch] = fmaf(w, xx[ch], P[j][7 + ch]);
+                P[j][10 + ch] = fmaf(w, yy[ch], P[j][10 + ch]);
+                P[j][13 + ch] = fmaf(w, xy[ch], P[j][13 + ch]);
+              }
+            }
+          }
+        });
+      };
+      if (pure) rows(SsBool<true>{});
+      else rows(SsBool<false>{});
+      // the halves' sums meet in LDS, over the patch
+      const int n0 = ss_nest_local(x, yp), n1 = ss_nest_local(x, yp + 1);
+      __syncthreads();
+      if (half == 0) {
+  #pragma unroll
+        for (int k = 0; k < 16; ++k) { S[k][n0] = P[0][k]; S[k][n1] = P[1][k]; }
+      }
+      __syncthreads();
+      if (half != 0) {
+  #pragma unroll
+        for (int k = 0; k < 16; ++k) { S[k][n0] += P[0][k]; S[k][n1] += P[1][k]; }
+      }
+      __syncthreads();
+  #pragma unroll
+      for (int k = 0; k < 16; ++k) Sm[k] = S[k][tid];
+    }
+    if (direct && !paired) {
       // direct 121-tap sums: polar pixels (zone windows) weigh by great-circle
       // distance, the others by the chart window
       if (more) load_cells(en, vn);
@@ -355,13 +465,16 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(SsimArgs A, const float* __res
       for (int k = 0; k < 16; ++k) Sm[k] = 0.f;
       if (own) {
         const bool polar = ZONES && ss_polar(A.order, hp_xyf_nest(A.order, x0 + px, y0 + py, f));
-        const double* up = s.dir[(py + SS_R) * H + px + SS_R];
+        const int cp = (py + SS_R) * H + px + SS_R;
+        const double up[3] = {s.dir[0][cp], s.dir[1][cp], s.dir[2][cp]};
         for (int b = 0; b < SS_W; ++b) {
           for (int a = 0; a < SS_W; ++a) {
             const int cy = py + b, cx = px + a;
             const float m = s.in[0][cy][cx];
             if (m == 0.f) continue;
-            const float w = polar ? m * __expf(-(float)(ss_dist2(up, s.dir[cy * H + cx]) * A.wscale))
+            const int cq = cy * H + cx;
+            const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
+            const float w = polar ? m * __expf(-(float)(ss_dist2(up, uq) * A.wscale))
                                   : m * (A.g[a] * A.g[b]);
             Sm[0] += w;
   #pragma unroll
@@ -482,7 +595,7 @@ struct SsBwdLds {
   static constexpr int H = B + 2 * SS_R, HP = (H + 3) & ~3, P1S = H * B + ((48 - (H * B) % 32) % 32);
   static_assert(B < 8 || 9 * P1S + 9 * B * B <= 9 * H * HP, "first-pass output and sums fit over the patch");
   float in[9][H][HP];
-  double dir[ZONES ? H * H : 1][3];
+  double dir[3][ZONES ? H * H : 1];
   uint8_t polar[ZONES ? H * H : 1];
 };
 
@@ -490,7 +603,7 @@ struct SsBwdLds {
 //   - lam / (3n) * sum_{q in W(p)} w_q(p) (G0_q + 2 x_p G1_q + y_p G2_q) ]
 // with w_q(p) the raw weight of q's window at p
 template <int B, bool ZONES>
-__global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs A, const float* __restrict__ img,
+__global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_bwd(SsimArgs A, const float* __restrict__ img,
                                                   const float* __restrict__ ref, const float* __restrict__ G,
                                                   const float* __restrict__ dL_dloss, float* __restrict__ dimg,
                                                   int n_tiles) {
@@ -535,7 +648,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs A, const float* __res
     const int ct = hp_xcd_tile(l, n_tiles);
     int f, x0, y0;
     ss_tile_origin(A, ct, &f, &x0, &y0);
-    bool any_polar = false;
+    bool any_polar = false, all_polar = true;  // all_polar: of the active cells
     __syncthreads();  // the previous tile's LDS reads are done
   #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
@@ -549,6 +662,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs A, const float* __res
           const bool pq = e[gi] >= 0 && (e[gi] & kSsPolarBit) != 0;
           s.polar[cy * H + cx] = pq ? 1 : 0;
           any_polar |= pq;
+          all_polar &= pq || e[gi] < 0;
         }
       }
     }
@@ -556,8 +670,13 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs A, const float* __res
     // tiles narrower than 8 pixels always take the direct path
     constexpr bool kSmall = B < 8;
     bool direct = kSmall;
-    if (ZONES) direct = __syncthreads_or(any_polar) || kSmall;
-    else __syncthreads();
+    bool pure = false;  // every window of the patch is a polar one
+    if (ZONES) {
+      pure = __syncthreads_and(all_polar);
+      direct = __syncthreads_or(any_polar) || kSmall;
+    } else {
+      __syncthreads();
+    }
     if (more) load_table(ln, en);
     const int px = (int)hp_compact_bits((uint32_t)tid), py = (int)hp_compact_bits((uint32_t)tid >> 1);
     float Sm[9];
@@ -623,24 +742,76 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(SsimArgs A, const float* __res
           const int64_t q = hp_chart_pixel(A.order, f, x0 + cx - SS_R, y0 + cy - SS_R);
           double d[3] = {0.0, 0.0, 0.0};
           if (q >= 0) hp_pix_dir(A.order, q, d);
-          s.dir[i][0] = d[0];
-          s.dir[i][1] = d[1];
-          s.dir[i][2] = d[2];
+          s.dir[0][i] = d[0];
+          s.dir[1][i] = d[1];
+          s.dir[2][i] = d[2];
         }
         __syncthreads();
       }
   #pragma unroll
       for (int k = 0; k < 9; ++k) Sm[k] = 0.f;
-      if (tid < B * B) {
-        const double* up = ZONES ? s.dir[(py + SS_R) * H + px + SS_R] : nullptr;
+      const bool paired = B == 16 && ZONES && A.fine;
+      if constexpr (B == 16 && ZONES) if (paired) {
+        const int half = (int)hp_uniform((uint32_t)tid >> 7);
+        const int x = tid & 15, yp = 2 * ((tid & 127) >> 4);
+        double h[2][3];
+  #pragma unroll
+        for (int j = 0; j < 2; ++j)
+  #pragma unroll
+          for (int c = 0; c < 3; ++c) h[j][c] = -0.5 * s.dir[c][(yp + j + SS_R) * H + x + SS_R];
+        float P[2][9];
+  #pragma unroll
+        for (int k = 0; k < 9; ++k) P[0][k] = P[1][k] = 0.f;
+        auto rows = [&](auto pure_tag) {
+          ss_pair_rows(half, [&](int b, auto up, auto low) {
+            constexpr bool on[2] = {decltype(up)::value, decltype(low)::value};
+            const int cell = (yp + b) * H + x, at = (yp + b) * L::HP + x;
+            const float* in = &s.in[0][0][0] + at;
+  #pragma unroll 1
+            for (int a = 0; a < SS_W; ++a) {
+              const double vx = s.dir[0][cell + a], vy = s.dir[1][cell + a], vz = s.dir[2][cell + a];
+              const bool pol = decltype(pure_tag)::value || s.polar[cell + a] != 0;
+              float g[9];
+  #pragma unroll
+              for (int k = 0; k < 9; ++k) g[k] = in[k * H * L::HP + a];
+  #pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                if (!on[j]) continue;
+                float w = ss_polar_weight(A, h[j], vx, vy, vz);
+                if constexpr (!decltype(pure_tag)::value) w = pol ? w : A.g[a] * A.g[b - j];
+  #pragma unroll
+                for (int k = 0; k < 9; ++k) P[j][k] = fmaf(w, g[k], P[j][k]);
+              }
+            }
+          });
+        };
+        if (pure) rows(SsBool<true>{});
+        else rows(SsBool<false>{});
+        const int n0 = ss_nest_local(x, yp), n1 = ss_nest_local(x, yp + 1);
+        __syncthreads();
+        if (half == 0) {
+  #pragma unroll
+          for (int k = 0; k < 9; ++k) { S[k][n0] = P[0][k]; S[k][n1] = P[1][k]; }
+        }
+        __syncthreads();
+        if (half != 0) {
+  #pragma unroll
+          for (int k = 0; k < 9; ++k) { S[k][n0] += P[0][k]; S[k][n1] += P[1][k]; }
+        }
+        __syncthreads();
+  #pragma unroll
+        for (int k = 0; k < 9; ++k) Sm[k] = S[k][tid];
+      }
+      if (!paired && tid < B * B) {
+        const int cp = ZONES ? (py + SS_R) * H + px + SS_R : 0;
+        const double up[3] = {s.dir[0][cp], s.dir[1][cp], s.dir[2][cp]};
         for (int b = 0; b < SS_W; ++b) {
           for (int a = 0; a < SS_W; ++a) {
-            const int cy = py + b, cx = px + a;
+            const int cy = py + b, cx = px + a, cq = ZONES ? cy * H + cx : 0;
+            const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
             // q's own window at p: the great-circle Gaussian for a polar q,
             // the (symmetric) chart taps otherwise
-            const float w = (ZONES && s.polar[cy * H + cx])
-                                ? __expf(-(float)(ss_dist2(up, s.dir[ZONES ? cy * H + cx : 0]) * A.wscale))
-                                : A.g[a] * A.g[b];
+            const float w = (ZONES && s.polar[cq]) ? __expf(-(float)(ss_dist2(up, uq) * A.wscale)) : A.g[a] * A.g[b];
   #pragma unroll
             for (int k = 0; k < 9; ++k) Sm[k] = fmaf(w, s.in[k][cy][cx], Sm[k]);
           }
@@ -771,6 +942,11 @@ static hp_status ssim_setup(const float* img, const float* ref, int64_t n_active
   }
   const double omega = 4.0 * M_PI / (double)g.npix;
   A->wscale = 1.0 / (2.0 * (double)sp->sigma * (double)sp->sigma * omega);
+  // exp(-d^2 wscale) = 2^(w2[0] s^2 + w2[1] s^4 + w2[2] s^6), d^2 = 4 s^2 (1 + s^2 / 3 + 8 s^4 / 45 ...)
+  A->w2[0] = -4.0 * A->wscale * 1.44269504088896340736;
+  A->w2[1] = A->w2[0] / 3.0;
+  A->w2[2] = A->w2[0] * (8.0 / 45.0);
+  A->fine = order >= kSsFineOrder && A->w2[0] * -5e-16 <= 6e-8;
   *Gm = (float*)ws;
   *part = (float2*)((char*)ws + hp_align256((size_t)kSsG * n_active * 4));
   return HP_OK;
