@@ -86,3 +86,29 @@ def test_cone_comes_from_the_mask(R):
     got, want = _lists(R, g, narrow, mask_cam=wide)
     _same(got, want)
     assert got[0].size == _lists(R, g, wide)[0][0].size
+
+
+@pytest.mark.parametrize("kind", ["full", "pinhole"])
+@pytest.mark.parametrize("P", [1, 63, 64, 65, 1023, 1024, 1025, 2048, 8191, 8192, 8193])
+def test_lists_in_depth_order(R, P, kind):
+    """Every tile's list by increasing depth and, among equal depths, by id,
+    at the edges of the one-workgroup depth sort (waves, rounds, its largest
+    scene and the first beyond), with a third of the depths shared."""
+    from paper_2606_29794_amd.raster import Camera, Gaussians
+    t, fx, fy = CAMS[kind]
+    rng = np.random.default_rng(P)
+    sc = SC.make_scene(P, 0, "log", 1.0, 20.0, 5 + P, log_scale_mu=-2.5, rng=rng)
+    twin = rng.integers(0, P, P // 3)
+    sc.mean[:, rng.choice(P, P // 3, replace=False)] = sc.mean[:, twin]
+    cam = Camera.from_dict(SC.make_camera(rng, 6, t, fov_x=math.radians(fx), fov_y=math.radians(fy)))
+    g = Gaussians.from_scene(sc)
+    proj = R.preprocess(g, cam)
+    depth = R.projected_arrays(proj, P)[1].cpu().numpy()
+    vals, ranges, n = R.bin_sorted(proj, P, cam)
+    v, r = vals[:n].cpu().numpy().astype(np.int64), ranges.cpu().numpy()[:R.mask(cam).n_tiles].astype(np.int64)
+    tile = np.full(n, -1)
+    for k, (a, b) in enumerate(r):
+        tile[a:b] = k
+    assert n == 0 or tile.min() >= 0
+    key = list(zip(tile.tolist(), depth[v].tolist(), v.tolist()))
+    assert all(a < b for a, b in zip(key, key[1:]) if a[0] == b[0])
