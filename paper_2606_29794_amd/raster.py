@@ -36,8 +36,16 @@ def _dense(t):
     return t.contiguous()
 
 
+def _raw_stream(device=None) -> int:
+    """Handle of the device's current stream, without the Python stream object
+    that torch.cuda.current_stream makes: a pass asks 15 times, at 2.5 us each
+    for the object and 0.3 us for the handle."""
+    index = None if device is None else device.index
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice() if index is None else index)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_raw_stream())
 
 
 def _bytes(n, device):
@@ -273,13 +281,12 @@ class Rasterizer:
     def _created(self, key):
         ev = torch.cuda.Event()
         ev.record(torch.cuda.current_stream(self.device))
-        self._ready[key] = (ev, torch.cuda.current_stream(self.device).cuda_stream)
+        self._ready[key] = (ev, _raw_stream(self.device))
 
     def _await(self, key):
         ev, sid = self._ready[key]
-        cur = torch.cuda.current_stream(self.device)
-        if cur.cuda_stream != sid:
-            cur.wait_event(ev)
+        if _raw_stream(self.device) != sid:
+            torch.cuda.current_stream(self.device).wait_event(ev)
 
     # ---- camera-independent tables ------------------------------------
     def grid(self, order: int) -> torch.Tensor:
@@ -349,7 +356,7 @@ class Rasterizer:
     def workspace(self, nbytes: int) -> torch.Tensor:
         """A scratch buffer of at least nbytes for work on the current stream
         (kept per stream and reused by the next call there)."""
-        sid = torch.cuda.current_stream(self.device).cuda_stream
+        sid = _raw_stream(self.device)
         with self._lock:
             ws = self._ws.get(sid)
             if ws is None or ws.numel() < nbytes:
@@ -562,8 +569,8 @@ class Rasterizer:
         if prepared is None:
             prepared = self.prepare(g, cam, query)
         else:
-            cur = torch.cuda.current_stream(self.device)
-            if cur.cuda_stream != prepared.stream_id:
+            if _raw_stream(self.device) != prepared.stream_id:
+                cur = torch.cuda.current_stream(self.device)
                 cur.wait_event(prepared.event)
                 # made on another stream, used (and freed) on this one
                 for t in (prepared.projected, prepared.vals, prepared.ranges, prepared.count.dev):
