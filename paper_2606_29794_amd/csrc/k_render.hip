@@ -261,7 +261,7 @@ template <bool DEPTH>
 __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs A, RenderOut O) {
   __shared__ float4 s_rec[2 * HP_STAGE];
   __shared__ float s_invd[2 * HP_CHUNK];
-  render_fwd_tile<DEPTH>(A, O, hp_xcd_tile(blockIdx.x, gridDim.x), s_rec, s_invd);
+  render_fwd_tile<DEPTH>(A, O, hp_xcd_group_tile(blockIdx.x, gridDim.x), s_rec, s_invd);
 }
 
 // Several requests in one launch: block b renders tile b - first[r] of
@@ -276,7 +276,7 @@ struct RenderBatch {
 
 __global__ __launch_bounds__(256) void k_render_fwd_batch(RenderBatch B) {
   __shared__ float4 s_rec[2 * HP_STAGE];
-  const int b = hp_xcd_tile(blockIdx.x, gridDim.x);
+  const int b = hp_xcd_group_tile(blockIdx.x, gridDim.x);
   int r = 0;
   while (r + 1 < B.n && b >= B.first[r + 1]) ++r;
   render_fwd_tile<false>(B.A[r], B.O[r], b - B.first[r], s_rec, nullptr);

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_fwd(SsimArgs A, con
   // and fetches the next tile's slot table and patch cells while the passes
   // of the current one run, so their latency is not waited out.
   auto load_table = [&](int l, int32_t* e) {
-    const int32_t* tab = A.tables + (int64_t)hp_xcd_tile(l, n_tiles) * (H * H);
+    const int32_t* tab = A.tables + (int64_t)(ZONES ? hp_xcd_group_tile(l, n_tiles) : hp_xcd_tile(l, n_tiles)) * (H * H);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
       const int i = tid + 256 * gi;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_fwd(SsimArgs A, con
   // one tile: the cells in e / v; with more, the next tile's (ln) are
   // fetched into en / vn during the passes
   auto tile = [&](int l, int ln, bool more) {
-    const int ct = hp_xcd_tile(l, n_tiles);
+    const int ct = (ZONES ? hp_xcd_group_tile(l, n_tiles) : hp_xcd_tile(l, n_tiles));
     int f, x0, y0;
     ss_tile_origin(A, ct, &f, &x0, &y0);
     // zone windows: the tile takes the direct path when it holds a polar pixel
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_bwd(SsimArgs A, con
   // tiles l = blockIdx.x, + gridDim.x, ... as in the forward; the next
   // tile's slot table and partials are fetched during the current passes
   auto load_table = [&](int l, int32_t* e) {
-    const int32_t* tab = A.tables + (int64_t)hp_xcd_tile(l, n_tiles) * (H * H);
+    const int32_t* tab = A.tables + (int64_t)(ZONES ? hp_xcd_group_tile(l, n_tiles) : hp_xcd_tile(l, n_tiles)) * (H * H);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
       const int i = tid + 256 * gi;
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 1) void k_ssim_bwd(SsimArgs A, con
   // one tile: the cells in e / v; with more, the next tile's (ln) are
   // fetched into en / vn during the passes
   auto tile = [&](int l, int ln, bool more) {
-    const int ct = hp_xcd_tile(l, n_tiles);
+    const int ct = (ZONES ? hp_xcd_group_tile(l, n_tiles) : hp_xcd_tile(l, n_tiles));
     int f, x0, y0;
     ss_tile_origin(A, ct, &f, &x0, &y0);
     bool any_polar = false, all_polar = true;  // all_polar: of the active cells
