@@ -289,7 +289,7 @@ __device__ __forceinline__ int hp_xcd_tile(int b, int nb) {
 // takes groups x, x + 8, ... of kXcdGroup neighbouring tiles, the tiles past the
 // last full round one by one.  A contiguous eighth of the sphere can hold 14 %
 // more work than the mean eighth, groups of 16 tiles hold within 1 % of it: forward
-// render 368 -> 352 us (full sphere, order 9), 376 -> 346 us (pinhole of 75
+// render 368 -> 352 us (full sphere, order 9), 376 -> 346 us (pinhole of 60
 // degrees, order 11), 119 -> 112 us (order 10), loss with zone windows, whose polar
 // tiles cost several others, 360 -> 331 us; groups of 4 and single tiles measured
 // the same within 2 %.  The backward's tiles add to shared accumulators and stay

@@ -1030,7 +1030,24 @@ __device__ __forceinline__ ChunkRange xcd_chunks(uint32_t n) {
   return r;
 }
 
+// w = 2 w + (the lane's bit of in[q]) for q = 0, 1, ...: one instruction each,
+// with the mask as carry-in; the compiler makes a select and an or of it. The
+// s_nop keeps the two wait states between a compare and its mask's use.
+static_assert(kFineGroup == 8, "shift_in_bits takes eight masks");
+__device__ __forceinline__ void shift_in_bits(uint32_t* w, const uint64_t* in) {
+#define HP_SHIFT_IN(n) "v_addc_co_u32_e64 %0, vcc, %0, %0, %" n "\n\t"
+  asm("s_nop 1\n\t" HP_SHIFT_IN("1") HP_SHIFT_IN("2") HP_SHIFT_IN("3") HP_SHIFT_IN("4") HP_SHIFT_IN("5")
+      HP_SHIFT_IN("6") HP_SHIFT_IN("7") HP_SHIFT_IN("8")
+      : "+v"(*w)
+      : "s"(in[0]), "s"(in[1]), "s"(in[2]), "s"(in[3]), "s"(in[4]), "s"(in[5]), "s"(in[6]), "s"(in[7])
+      : "vcc");
+#undef HP_SHIFT_IN
+}
+
 // per chunk: the hit columns W_b (kept) and their popcounts, tile-major
+// Bound by vector instruction issue, 11 per (task, 64 leaves): 107 -> 76 us (1M
+// Gaussians on the full sphere at Nside 512), 68 -> 48 us (3M, pinhole of 60
+// degrees at Nside 2048) since the bits are shifted in.
 __global__ __launch_bounds__(256) void k_bin_cols(const uint32_t* __restrict__ choff, uint32_t nn,
                                                   const uint32_t* __restrict__ seg, const uint32_t* __restrict__ cnode,
                                                   const uint32_t* __restrict__ tgid,
@@ -1076,13 +1093,16 @@ __global__ __launch_bounds__(256) void k_bin_cols(const uint32_t* __restrict__ c
     // sphere keeps the full test
     const float srl = hp_wave_max(h.x);
     const uint64_t nearmask = __builtin_amdgcn_ballot_w64(!((uint32_t)lane < ntask) || cgl > srl + kNearMargin);
-    // bits of tasks 0..31 and 32..63 are kept apart so that every set is a
-    // 32-bit select-or
+    // A task's decisions are a wave mask (one lane per leaf); every lane shifts its
+    // bit into its column with one add-with-carry, W = 2 W + bit (as a select and an
+    // or it took two and a half instructions a task, of 12.5). After r groups
+    // the last task of a half stands at bit 0 and the first at bit 8 r - 1.
     uint32_t Wh[2] = {0u, 0u};
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       const uint32_t jend = ntask < 32u * (half + 1) ? ntask : 32u * (half + 1);
-      for (uint32_t j0 = 32u * half; j0 < jend; j0 += kFineGroup) {
+      uint32_t w = 0u, j0 = 32u * half;
+      for (; j0 < jend; j0 += kFineGroup) {
         // entries past the chunk's end are read too (stale or zero LDS, in
         // bounds) and their bits dropped, so the reads take fixed offsets
         auto group = [&](auto near_tag) {
@@ -1094,19 +1114,22 @@ __global__ __launch_bounds__(256) void k_bin_cols(const uint32_t* __restrict__ c
             ux[q] = d.x; uy[q] = d.y; uz[q] = d.z; sg[q] = d.w;
             cg[q] = s_cg[wv][j0 + q];
           }
+          uint64_t in[kFineGroup];
 #pragma unroll
-          for (int q = 0; q < kFineGroup; ++q) {
-            const bool in = NEAR ? hp_cap_test_near(cx, cy, cz, h.x, h.y, ux[q], uy[q], uz[q], sg[q], cg[q])
-                                 : hp_cap_test(cx, cy, cz, h.x, h.y, ux[q], uy[q], uz[q], sg[q], cg[q]);
-            const uint32_t bit = j0 + q < jend ? (1u << ((j0 + q) & 31u)) : 0u;
-            Wh[half] |= in ? bit : 0u;
-          }
+          for (int q = 0; q < kFineGroup; ++q)
+            in[q] = __builtin_amdgcn_ballot_w64(
+                NEAR ? hp_cap_test_near(cx, cy, cz, h.x, h.y, ux[q], uy[q], uz[q], sg[q], cg[q])
+                     : hp_cap_test(cx, cy, cz, h.x, h.y, ux[q], uy[q], uz[q], sg[q], cg[q]));
+          shift_in_bits(&w, in);
         };
         if (((nearmask >> j0) & 0xffull) == 0xffull)
           group(std::true_type{});
         else
           group(std::false_type{});
       }
+      // task 32 half + j to bit j, bits past the chunk's end dropped
+      const uint32_t done = j0 - 32u * half, cnt_h = jend - 32u * half;
+      if (done != 0u) Wh[half] = (__builtin_bitreverse32(w) >> (32u - done)) & (~0u >> (32u - cnt_h));
     }
     const uint64_t W = act ? ((uint64_t)Wh[1] << 32) | Wh[0] : 0ull;
     if (leaf_lane) {
