@@ -349,6 +349,7 @@ __global__ __launch_bounds__(256) void k_bin_coarse(int64_t P, const uint64_t* _
 // of the depth-ordered tasks by node gives.
 constexpr int kWalkGroup = 768;
 constexpr int kListNodes = 4 * kWalkGroup;
+constexpr int kWalkSmall = 192;  // nodes of the split levels up to 2: LDS for these alone (k_task_walk)
 constexpr int kStageFixed = 4096;  // staged tasks per 256 Gaussians; the rest overflow
 static_assert(kListNodes <= 12 * 256, "k_task_segments takes twelve nodes per thread");
 
@@ -375,7 +376,7 @@ struct TaskStage {
 // bounded grid (what is resident at once) loop: a launch of one workgroup per 256 Gaussians of
 // the scene spent tens of microseconds on starting idle ones when a narrow
 // view keeps an eighth of the scene.
-constexpr unsigned kWalkGrid = 768, kPlaceGrid = 1024;
+constexpr unsigned kWalkGrid = 768, kWalkGridSmall = 1024, kPlaceGrid = 1024;
 static unsigned walk_grid(unsigned G, unsigned most) { return G < most ? (G + 255u) & ~255u : most; }
 __device__ __forceinline__ int64_t walk_first(uint32_t h) {
   const uint32_t x = h & 7u, k = h >> 3;
@@ -390,7 +391,7 @@ __device__ __forceinline__ int64_t walk_first(uint32_t h) {
 // that walked them alone held up its wave: 250K Gaussians seen by a 75-degree
 // pinhole at Nside 1024 took 105 us to count and 219 us to place, one lane's
 // chain of dependent tests; the shared stack makes that 38 and 11 us (1M
-// Gaussians on the full sphere at Nside 512: 72 + 122 us became 95 + 30 us).
+// Gaussians on the full sphere at Nside 512: 72 + 122 us became 77 + 30 us).
 // Four lanes to a parent read its four children's caps as one 64-byte line.
 // The same nodes pass as in coarse_nodes: the faces, which that walk does not
 // test, are tested with a margin (a face's cap contains its descendants'), so
@@ -407,16 +408,19 @@ __device__ __forceinline__ int64_t walk_first(uint32_t h) {
 // deeper levels, so going up the stack each batch holds deeper levels only, and
 // at most 192 entries remain of each of the levels 1 to ls - 1 above at most 63
 // faces: 63 + 192 + 192 + 256 = 703 at ls = 4.
-// Bound by VALU issue (1,690 instructions per 64 Gaussians, 43 of the 95 us)
-// and latency; 52 KB of LDS, three workgroups per CU.
-constexpr int kWalkRow = kWalkGroup + 8;  // pitch of the bit matrix: its eight words of a node in different banks
+// Bound by vector issue (1,690 instructions per 64 Gaussians, 45 us of the case
+// above) and latency: 52 KB of LDS for 768 nodes, three workgroups per CU, 94 us;
+// with LDS for the 192 nodes that split levels up to 2 have, 31 KB and four
+// workgroups (118 registers), 77 us; five, held to 96 registers, the same.
 constexpr int kWalkStack = 704;  // entries per wave: Gaussian of the wave << 10 | heap index
 constexpr int kWalkList = 1024;  // tasks listed per wave: node << 6 | Gaussian of the wave
+template <int GROUP>
 struct WalkLds {
+  static constexpr int kRow = GROUP + 8;  // pitch of the bit matrix: its eight words of a node in different banks
   float4 cap[kTopNodes];  // levels 0..2: centre and sin(R/2)
   float cr[kTopNodes];    // cos(R/2); NaN for inactive nodes, which then pass no test
-  uint32_t bits[8][kWalkRow];
-  uint32_t cnt[kWalkGroup];  // tasks per node
+  uint32_t bits[8][kRow];
+  uint32_t cnt[GROUP];  // tasks per node
   uint16_t list[4][kWalkList];
   uint16_t stack[4][kWalkStack];
   union {
@@ -425,24 +429,26 @@ struct WalkLds {
       float cg[256];
     };
     struct {  // after the walk
-      uint32_t start[kWalkGroup];  // the node's first place in the run
+      uint32_t start[GROUP];  // the node's first place in the run
       uint32_t gid[256];
     };
   };
 };
+template <int GROUP>
 __global__ __launch_bounds__(256) void k_task_walk(const uint64_t* __restrict__ n_live,
                                                    const uint32_t* __restrict__ order,
                                                    const float4* __restrict__ disc, BinTables T, int nn, int64_t G,
                                                    uint32_t* __restrict__ hist, TaskStage st) {
-  __shared__ WalkLds s;
+  constexpr int kRow = WalkLds<GROUP>::kRow, kPer = (GROUP + 255) / 256;
+  __shared__ WalkLds<GROUP> s;
   __shared__ uint32_t s_w[4], s_listed[4];
   __shared__ uint64_t s_ob;
   const int64_t n_in = (int64_t)*n_live;
   const int64_t bfirst = walk_first(blockIdx.x);
   if (bfirst * 256 >= n_in) return;
   const int tid = threadIdx.x, wv = tid >> 6, lane = hp_lane();
-  const int n0 = (int)blockIdx.y * kWalkGroup;
-  const int ng = nn - n0 < kWalkGroup ? nn - n0 : kWalkGroup;
+  const int n0 = (int)blockIdx.y * GROUP;
+  const int ng = nn - n0 < GROUP ? nn - n0 : GROUP;
   const int nroot = 12 / (int)gridDim.y, root0 = (int)blockIdx.y * nroot;  // the group's faces
   bool any = !T.node_active;
   if (T.node_active)
@@ -484,8 +490,8 @@ __global__ __launch_bounds__(256) void k_task_walk(const uint64_t* __restrict__ 
   for (int64_t b = bfirst; b * 256 < n_in; b += gridDim.x) {
     const int64_t vb = (int64_t)blockIdx.y * G + b;
     __syncthreads();  // the previous block's reads are done
-    for (int i = tid; i < 8 * kWalkRow / 4; i += 256) reinterpret_cast<uint4*>(&s.bits[0][0])[i] = make_uint4(0, 0, 0, 0);
-    for (int i = tid; i < kWalkGroup; i += 256) s.cnt[i] = 0u;
+    for (int i = tid; i < 8 * kRow / 4; i += 256) reinterpret_cast<uint4*>(&s.bits[0][0])[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < GROUP; i += 256) s.cnt[i] = 0u;
     const uint32_t gid = gid_next;
     const float4 dg = dg_next;
     const bool live = dg.w > 0.f;
@@ -579,12 +585,12 @@ __global__ __launch_bounds__(256) void k_task_walk(const uint64_t* __restrict__ 
     }
     if (lane == 0) s_listed[wv] = nlist <= kWalkList;
     __syncthreads();
-    // the node counts to the histogram, and scanned (thread t: nodes 3t .. 3t + 2)
+    // the node counts to the histogram, and scanned (thread t: kPer nodes from kPer t)
     s.gid[tid] = gid;
-    uint32_t cnt[3], sum = 0;
+    uint32_t cnt[kPer], sum = 0;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int n = 3 * tid + q;
+    for (int q = 0; q < kPer; ++q) {
+      const int n = kPer * tid + q;
       cnt[q] = n < ng ? s.cnt[n] : 0u;
       if (n < ng) hist[(int64_t)(n0 + n) * G + b] = cnt[q];
       sum += cnt[q];
@@ -592,8 +598,8 @@ __global__ __launch_bounds__(256) void k_task_walk(const uint64_t* __restrict__ 
     uint32_t total;
     uint32_t pos = hpsort::block_exclusive<uint32_t>(sum, &total, s_w);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      if (3 * tid + q < ng) s.start[3 * tid + q] = pos;
+    for (int q = 0; q < kPer; ++q) {
+      if (kPer * tid + q < ng) s.start[kPer * tid + q] = pos;
       pos += cnt[q];
     }
     const uint32_t fixed = (uint32_t)st.fixed;
@@ -1651,9 +1657,13 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
       st.ocount = w.n_over;
       st.ocap = w.cap_t;
       st.fixed = kStageFixed / (int)groups;
-      const dim3 wg(walk_grid(G, kWalkGrid), groups), pg(walk_grid(G, kPlaceGrid), groups);
-      hipLaunchKernelGGL(k_task_walk, wg, dim3(256), 0, s, (const uint64_t*)w.n_live, (const uint32_t*)w.order, pv.disc,
-                         T, nni, (int64_t)G, hist, st);
+      const dim3 wg(walk_grid(G, nni <= kWalkSmall ? kWalkGridSmall : kWalkGrid), groups), pg(walk_grid(G, kPlaceGrid), groups);
+      if (nni <= kWalkSmall)
+        hipLaunchKernelGGL(k_task_walk<kWalkSmall>, wg, dim3(256), 0, s, (const uint64_t*)w.n_live,
+                           (const uint32_t*)w.order, pv.disc, T, nni, (int64_t)G, hist, st);
+      else
+        hipLaunchKernelGGL(k_task_walk<kWalkGroup>, wg, dim3(256), 0, s, (const uint64_t*)w.n_live,
+                           (const uint32_t*)w.order, pv.disc, T, nni, (int64_t)G, hist, st);
       HP_CHECK_LAUNCH();
       hipLaunchKernelGGL(k_hist_rows, dim3(nni), dim3(256), 0, s, (const uint32_t*)hist, (int64_t)G,
                          (const uint64_t*)w.n_live, T.node_active ? T.node_active + hp_level_offset(ls) : nullptr, hoff,
