@@ -130,12 +130,12 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const In* __restrict__
 // thread scans 16 consecutive elements of it, and the results leave striped
 // again.  LDS element i sits at i + i / 16, so that the 16-element runs of
 // neighbouring threads start in different banks.
-template <class T, class In>
-__global__ __launch_bounds__(kThreads) void k_scan_down(const In* in, T* out, const uint64_t* __restrict__ cnt,
+template <class T, class In, class Out>
+__global__ __launch_bounds__(kThreads) void k_scan_down(const In* in, Out* out, const uint64_t* __restrict__ cnt,
                                                         int64_t cap, const T* __restrict__ sums, T* grand,
                                                         int64_t* count_out, const uint32_t* __restrict__ over) {
   __shared__ T s_w[4];
-  __shared__ T s_x[kTile + kTile / kItems];
+  __shared__ Out s_x[kTile + kTile / kItems];
   const int64_t n = dev_count(cnt, cap);
   int64_t t0, t1;
   block_tiles(n, &t0, &t1);
@@ -159,10 +159,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const In* in, T* out, co
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
       const int i = k * kThreads + (int)threadIdx.x;
-      s_x[i + i / kItems] = tb + i < n ? (T)in[tb + i] : T(0);
+      s_x[i + i / kItems] = tb + i < n ? (Out)in[tb + i] : Out(0);
     }
     __syncthreads();
-    T v[kItems];
+    Out v[kItems];
     T acc = 0;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const In* in, T* out, co
     T ex = block_exclusive<T>(acc, &tile_total, s_w) + carry;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      s_x[run + k] = ex;
+      s_x[run + k] = (Out)ex;
       ex += v[k];
     }
     __syncthreads();
@@ -196,16 +196,16 @@ inline size_t scan_ws_bytes(int64_t cap) {
 // T) into `out` (in place allowed); *grand (device, nullable) receives the
 // total.  cnt null: cap elements.  With count_out (device, nullable; then
 // `over` too) *count_out receives the total as int64, or INT64_MAX when *over
-// is set.
-template <class T, class In>
-inline hp_status scan_exclusive(const In* in, T* out, const uint64_t* cnt, int64_t cap, T* grand, void* ws,
+// is set.  Out narrower than T holds the prefixes modulo its range.
+template <class T, class In, class Out = T>
+inline hp_status scan_exclusive(const In* in, Out* out, const uint64_t* cnt, int64_t cap, T* grand, void* ws,
                                 hipStream_t s, int64_t* count_out = nullptr, const uint32_t* over = nullptr) {
   if (cap < 0) return HP_ERR_INVALID_ARG;
   const unsigned G = grid_for(cap);
   T* sums = (T*)ws;
   hipLaunchKernelGGL((k_scan_reduce<T, In>), dim3(G), dim3(kThreads), 0, s, in, cnt, cap, sums);
   HP_CHECK_LAUNCH();
-  hipLaunchKernelGGL((k_scan_down<T, In>), dim3(G), dim3(kThreads), 0, s, in, out, cnt, cap, (const T*)sums, grand,
+  hipLaunchKernelGGL((k_scan_down<T, In, Out>), dim3(G), dim3(kThreads), 0, s, in, out, cnt, cap, (const T*)sums, grand,
                      count_out, over);
   HP_CHECK_LAUNCH();
   return HP_OK;

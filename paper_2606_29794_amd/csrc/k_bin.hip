@@ -1153,6 +1153,10 @@ __global__ __launch_bounds__(256) void k_bin_cols(const uint32_t* __restrict__ c
 // whose rank in its column gives the slot.  So each store instruction is
 // full (the slots of one column are consecutive), where a store per column
 // would carry ~10 lanes.
+// Bound by LDS round trips and, on long lists, by the 4 B written per pair:
+// 73 -> 68 us (full sphere, order 9, 1M Gaussians) and 100 -> 95 us (pinhole of 60
+// degrees, order 11, 3M, some 75M pairs) with 32-bit slots; listing the hits in
+// windows of 1,024, for twice the workgroups per CU, measured 76 and 124 us.
 constexpr int kMaxChunkHits = 64 * 64;
 
 // (start, end) of every active tile from the scanned column counts; the end
@@ -1168,7 +1172,7 @@ struct TileRanges {
   uint32_t* ranges;
 };
 __device__ __forceinline__ void write_tile_ranges(const TileRanges& R, int depth, const uint32_t* __restrict__ choff,
-                                                  const uint64_t* __restrict__ start, bool none) {
+                                                  const uint32_t* __restrict__ start, bool none) {
   const int nleaf = 1 << (2 * depth);
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < R.n_tiles;
        k += (int64_t)gridDim.x * blockDim.x) {
@@ -1182,8 +1186,8 @@ __device__ __forceinline__ void write_tile_ranges(const TileRanges& R, int depth
     const int64_t c0 = choff[n], nchn = (int64_t)choff[n + 1] - c0;
     const uint64_t nc = *R.ncol;
     const uint64_t i0 = (uint64_t)(c0 * nleaf + b * nchn), i1 = (uint64_t)(c0 * nleaf + (b + 1) * nchn);
-    R.ranges[2 * k] = (uint32_t)(i0 < nc ? start[i0] : *R.total);
-    R.ranges[2 * k + 1] = (uint32_t)(i1 < nc ? start[i1] : *R.total);
+    R.ranges[2 * k] = i0 < nc ? start[i0] : (uint32_t)*R.total;
+    R.ranges[2 * k + 1] = i1 < nc ? start[i1] : (uint32_t)*R.total;
   }
 }
 
@@ -1192,15 +1196,14 @@ __global__ __launch_bounds__(256) void k_bin_emit_sorted(const uint32_t* __restr
                                                          const uint32_t* __restrict__ cnode,
                                                          const uint32_t* __restrict__ tgid, int depth,
                                                          const uint64_t* __restrict__ wcol,
-                                                         const uint64_t* __restrict__ start,
+                                                         const uint32_t* __restrict__ start,
                                                          const int64_t* __restrict__ n_pairs, int64_t capacity,
                                                          uint32_t* __restrict__ vals, TileRanges tr) {
   const bool none = *n_pairs > capacity;
   write_tile_ranges(tr, depth, choff, start, none);
   if (none) return;
-  __shared__ uint64_t s_base[4][64];
-  __shared__ uint32_t s_g[4][64], s_off[4][64];
-  __shared__ uint16_t s_hit[4][kMaxChunkHits];  // column << 8 | task of every hit number
+  __shared__ uint32_t s_g[4][64], s_slot[4][64];  // slot of column b's hit number k: s_slot[b] + k
+  __shared__ uint16_t s_hit[4][kMaxChunkHits];    // column << 8 | task of every hit number
   const uint32_t nchunks = hp_uniform(((hp_cu32p)choff)[nn]);
   const int lane = hp_lane();
   const int wv = threadIdx.x >> 6;
@@ -1208,28 +1211,30 @@ __global__ __launch_bounds__(256) void k_bin_emit_sorted(const uint32_t* __restr
   const bool leaf_lane = lane < nleaf;
   const ChunkRange cr = xcd_chunks(nchunks);
   // a chunk's columns, output slots and Gaussian ids
-  auto fetch = [&](uint32_t c, uint64_t* W, uint64_t* base, uint32_t* g) {
+  auto fetch = [&](uint32_t c, uint64_t* W, uint32_t* base, uint32_t* g) {
     const ChunkInfo ci = chunk_info(choff, seg, cnode, c);
     *W = leaf_lane ? wcol[(int64_t)c * 64 + lane] : 0ull;
-    *base = leaf_lane ? start[(int64_t)(c - ci.local) * nleaf + (int64_t)lane * ci.nchn + ci.local] : 0ull;
+    *base = leaf_lane ? start[(int64_t)(c - ci.local) * nleaf + (int64_t)lane * ci.nchn + ci.local] : 0u;
     *g = (uint32_t)lane < ci.ntask ? tgid[ci.t0 + lane] : 0u;
   };
   uint32_t c = cr.first;
   if (c >= cr.end) return;
-  uint64_t W, base;
-  uint32_t g;
+  uint64_t W;
+  uint32_t base, g;
   fetch(c, &W, &base, &g);
   while (true) {
     // the next chunk's loads go out before this chunk's stores
     const uint32_t cn = c + cr.stride;
     const bool more = cn < cr.end;
-    uint64_t Wn = 0ull, basen = 0ull;
-    uint32_t gn = 0u;
+    uint64_t Wn = 0ull;
+    uint32_t basen = 0u, gn = 0u;
     if (more) fetch(cn, &Wn, &basen, &gn);
     const uint32_t cnt = (uint32_t)__popcll(W);
     const uint32_t incl = hpsort::wave_inclusive<uint32_t>(cnt);
     const uint32_t off = incl - cnt;
     const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    s_g[wv][lane] = g;
+    s_slot[wv][lane] = base - off;
     // column lane b: its hits at numbers off, off + 1, ... (every number
     // below tot written once)
     {
@@ -1240,14 +1245,10 @@ __global__ __launch_bounds__(256) void k_bin_emit_sorted(const uint32_t* __restr
         w &= w - 1;
       }
     }
-    s_base[wv][lane] = base;
-    s_g[wv][lane] = g;
-    s_off[wv][lane] = off;
     __builtin_amdgcn_wave_barrier();
     for (uint32_t k = (uint32_t)lane; k < tot; k += 64) {
       const uint32_t e = s_hit[wv][k];
-      const uint32_t b = e >> 8;
-      vals[s_base[wv][b] + (k - s_off[wv][b])] = s_g[wv][e & 0xffu];
+      vals[s_slot[wv][e >> 8] + k] = s_g[wv][e & 0xffu];
     }
     __builtin_amdgcn_wave_barrier();  // this chunk's LDS reads are done
     if (!more) break;
@@ -1538,7 +1539,7 @@ struct SortedWs {
   uint32_t* nch;     // [nn] chunks per node
   uint32_t* choff;   // [nn + 1] first chunk of every node, total last
   uint32_t* cnt;     // [L] hits per (chunk, leaf), tile-major
-  uint64_t* start;   // [L] exclusive scan of cnt: first output slot
+  uint32_t* start;   // [L] exclusive scan of cnt: first output slot, modulo 2^32 (a list that long is not emitted)
   uint64_t* wcol;    // [nchunk_max][64] hit columns
   uint32_t* slots;   // [kSlots][P] first task nodes of every Gaussian (coarse walk)
   uint32_t* cnode;   // [nchunk_max] node of every chunk
@@ -1558,7 +1559,7 @@ static size_t sorted_ws_size(int64_t P, const HpGeom& g) {
   int64_t nn, ncm, L;
   sorted_dims(P, g, &nn, &ncm, &L);
   return hpsort::radix_ws_bytes(task_capacity(P)) + hp_align256(nn * 8) + hp_align256(nn * 4) +
-         hp_align256((nn + 1) * 4) + hp_align256(L * 4) + hp_align256(L * 8) + hp_align256(ncm * 64 * 8) +
+         hp_align256((nn + 1) * 4) + hp_align256(L * 4) + hp_align256(L * 4) + hp_align256(ncm * 64 * 8) +
          hp_align256((size_t)kSlots * P * 4) + hp_align256((size_t)ncm * 4) +
          hpsort::scan_ws_bytes<uint64_t>(L > nn ? L : nn);
 }
@@ -1572,7 +1573,7 @@ static SortedWs sorted_ws(void* base, int64_t P, const HpGeom& g) {
   w.nch = (uint32_t*)p; p += hp_align256(w.nn * 4);
   w.choff = (uint32_t*)p; p += hp_align256((w.nn + 1) * 4);
   w.cnt = (uint32_t*)p; p += hp_align256(w.L * 4);
-  w.start = (uint64_t*)p; p += hp_align256(w.L * 8);
+  w.start = (uint32_t*)p; p += hp_align256(w.L * 4);
   w.wcol = (uint64_t*)p; p += hp_align256(w.nchunk_max * 64 * 8);
   w.slots = (uint32_t*)p; p += hp_align256((size_t)kSlots * P * 4);
   w.cnode = (uint32_t*)p; p += hp_align256((size_t)w.nchunk_max * 4);
@@ -1711,7 +1712,7 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
     HP_CHECK_LAUNCH();
     // the pair total goes to *n_pairs with the scan (a count no buffer holds
     // when the tasks overflowed: the emission kernels then write nothing)
-    HP_TRY((hpsort::scan_exclusive<uint64_t, uint32_t>(sw.cnt, sw.start, w.ncol, sw.L, w.p_total, sw.scan_ws, s,
+    HP_TRY((hpsort::scan_exclusive<uint64_t, uint32_t, uint32_t>(sw.cnt, sw.start, w.ncol, sw.L, w.p_total, sw.scan_ws, s,
                                                        n_pairs, (const uint32_t*)w.over)));
   }
   if ((phase & HP_BIN_EMIT) && P > 0) {
@@ -1720,7 +1721,7 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
     const TileRanges tr{n_tiles, mv.active_tiles, (const uint64_t*)w.ncol, (const uint64_t*)w.p_total, tile_ranges};
     hipLaunchKernelGGL(k_bin_emit_sorted, dim3(chunk_grid(sw.nchunk_max)), dim3(256), 0, s, (const uint32_t*)sw.choff,
                        nn, (const uint32_t*)sw.seg, (const uint32_t*)sw.cnode, (const uint32_t*)w.task_g, depth,
-                       (const uint64_t*)sw.wcol, (const uint64_t*)sw.start, (const int64_t*)n_pairs, capacity, vals, tr);
+                       (const uint64_t*)sw.wcol, (const uint32_t*)sw.start, (const int64_t*)n_pairs, capacity, vals, tr);
     HP_CHECK_LAUNCH();
   } else if ((phase & HP_BIN_EMIT) && n_tiles > 0) {
     hipLaunchKernelGGL(k_fill_zero_u32, dim3(hp_blocks(2 * (int64_t)n_tiles, 256)), dim3(256), 0, s, tile_ranges,
