@@ -292,8 +292,8 @@ __device__ __forceinline__ int hp_xcd_tile(int b, int nb) {
 // render 368 -> 352 us (full sphere, order 9), 376 -> 346 us (pinhole of 60
 // degrees, order 11), 119 -> 112 us (order 10), loss with zone windows, whose polar
 // tiles cost several others, 360 -> 331 us; groups of 4 and single tiles measured
-// the same within 2 %.  The backward's tiles add to shared accumulators and stay
-// contiguous: with groups 144 -> 155 us on a fisheye of order 8.
+// the same within 2 %.  A backward whose tiles add to value-major
+// accumulators stays contiguous: with groups 144 -> 155 us on a fisheye of order 8.
 constexpr int kXcdGroup = 16;
 __device__ __forceinline__ int hp_xcd_group_tile(int b, int nb) {
   constexpr int G = kXcdGroup;

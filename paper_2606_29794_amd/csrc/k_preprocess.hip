@@ -209,7 +209,7 @@ template <int DEG>
 __global__ __launch_bounds__(256) void k_preprocess_bwd(int64_t P, const float* __restrict__ mean,
                                                         const float* __restrict__ scale, const float* __restrict__ rot,
                                                         const float* __restrict__ sh, HpViewK V, float r_min,
-                                                        float sh_off, const float* __restrict__ acc,
+                                                        float sh_off, const float* __restrict__ acc, bool packed,
                                                         float* __restrict__ gmean, float* __restrict__ gscale,
                                                         float* __restrict__ grot, float* __restrict__ gopac,
                                                         float* __restrict__ gsh) {
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(int64_t P, const float* 
   bool any = false;
 #pragma unroll
   for (int m = 0; m < 10; ++m) {
-    gy[m] = acc[m * P + i];
+    gy[m] = packed ? acc[10 * i + m] : acc[m * P + i];
     any = any || gy[m] != 0.f;
   }
   if (!any) return;
@@ -382,12 +382,12 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(int64_t P, const float* 
 }
 
 hp_status hp_preprocess_bwd_launch(const hp_gaussians* g, const hp_view* view, const hp_params* prm, const float* acc,
-                                   hp_gaussians_grad* grad, hipStream_t s) {
+                                   bool packed, hp_gaussians_grad* grad, hipStream_t s) {
   const dim3 grid(hp_blocks(g->P, 256)), block(256);
   const HpViewK vk = hp_viewk(view);
 #define HP_PRE_BWD(D)                                                                                                \
   hipLaunchKernelGGL(k_preprocess_bwd<D>, grid, block, 0, s, g->P, g->mean, g->scale, g->rot, g->sh, vk, prm->r_min, \
-                     prm->sh_offset, acc, grad->mean, grad->scale, grad->rot, grad->opacity, grad->sh)
+                     prm->sh_offset, acc, packed, grad->mean, grad->scale, grad->rot, grad->opacity, grad->sh)
   switch (g->sh_degree) {
     case 0: HP_PRE_BWD(0); break;
     case 1: HP_PRE_BWD(1); break;

@@ -286,6 +286,12 @@ __global__ __launch_bounds__(256) void k_render_fwd_batch(RenderBatch B) {
 // [0..2] colour, [3] opacity, [4..6] conic (A, B, C), [7] omega, [8] phi,
 // [9] inverse radial depth 1/r (written only with a depth gradient).
 #define HP_NACC 10
+// dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa - hc a)
+// from an entry's totals S and its record; the first sum is (A - C) S5 + B (S6 - S4)
+__device__ __forceinline__ float flush_omega(const float* S, const float4* rec) {
+  const float4 r2 = rec[2];
+  return rec[1].w * S[7] - rec[0].y * ((r2.y - r2.w) * S[5] + r2.z * (S[6] - S[4]));
+}
 template <bool B>
 struct HpBool {
   static constexpr bool value = B;
@@ -303,7 +309,14 @@ struct HpBool {
 // DEPTH: the upstream gradient also holds dL/d(inverse depth) per pixel; the
 // inverse depth enters the compositing like a colour channel, and the tenth
 // accumulator receives dL/d(1/r) per Gaussian.
-template <bool DEPTH>
+// PACKED: acc holds the ten values of a Gaussian side by side ([P][10]), which
+// a flush adds as one or two cache lines per entry instead of nine; the atomics
+// were 25 of 142 us on a fisheye of order 8 and 150 of 765 us on the full sphere.
+// Fewer lines also let the tiles interleave over the XCDs
+// (hp_xcd_group_tile): 142 -> 123 us and 766 -> 708 us per view.  Otherwise
+// [10][P], the layout that hp_render_bwd_pixels promises, with contiguous tiles
+// (pinhole with depth: 276 -> 271 us by the flush's fewer registers).
+template <bool DEPTH, bool PACKED>
 __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, const float* __restrict__ Tfin,
                                                     const int32_t* __restrict__ ncon, const float* __restrict__ gC,
                                                     const float* __restrict__ gTfin, const float* __restrict__ gDinv,
@@ -316,7 +329,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
   __shared__ float s_acc[HP_CHUNK * NA];
   __shared__ uint32_t s_gid[2][HP_CHUNK];  // Gaussian id of every staged entry
   __shared__ float s_invd[2][HP_CHUNK];    // 1/r of every staged entry (DEPTH)
-  const int ct = hp_xcd_tile(blockIdx.x, gridDim.x);
+  const int ct = PACKED ? hp_xcd_group_tile(blockIdx.x, gridDim.x) : hp_xcd_tile(blockIdx.x, gridDim.x);
   bool valid;
   int64_t slot;
   float p[3];
@@ -486,43 +499,22 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
     if (qs == 3) s_gid[(ctop - ch + 1) & 1][e] = gstage;
     if (DEPTH && qs == 2) s_invd[(ctop - ch + 1) & 1][e] = 1.f / dstage;
     __syncthreads();  // the chunk's totals are complete and the next chunk is staged
-    // Four threads of a wave per entry send its non-zero totals and clear them
-    // (each thread's reads come before any of the wave's writes): thread qs = 0
-    // the colours, 1 opacity, dL/dphi and the inverse depth, 2 the conic, 3
-    // dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa
-    // - hc a); the first sum is (A - C) S5 + B (S6 - S4) in the totals S4..S6
-    {
-      float* S = s_acc + e * NA;
-      const uint32_t g = s_gid[(ctop - ch) & 1][e];
-      float x0, x1 = 0.f, x2 = 0.f;
-      int m0, m1 = 0, m2 = 0;
-      if (qs == 0) {
-        x0 = S[0]; x1 = S[1]; x2 = S[2];
-        m0 = 0; m1 = 1; m2 = 2;
-      } else if (qs == 1) {
-        x0 = S[3]; x1 = S[8];
-        m0 = 3; m1 = 8;
-        if constexpr (DEPTH) { x2 = S[9]; m2 = 9; }
-      } else {
-        x0 = S[4]; x1 = S[5]; x2 = S[6];
-        m0 = 4; m1 = 5; m2 = 6;
-      }
-      if (qs == 3) {
-        const float4 r2 = cur[4 * e + 2];
-        x0 = cur[4 * e + 1].w * S[7] - cur[4 * e].y * ((r2.y - r2.w) * x1 + r2.z * (x2 - x0));
-        x1 = x2 = 0.f;
-        m0 = 7;
-      }
-      if (qs == 2) {  // constant factors of the conic's values
-        x0 *= -0.5f;
-        x1 = -x1;
-        x2 *= -0.5f;
-      }
+    // Sixteen threads of a wave per entry, thread m for value m: the non-zero
+    // totals are sent and cleared (every read of an entry's totals comes before
+    // any of its writes).  Kept a loop: unrolled it held the kernel at 79 registers
+    // and 6 waves per SIMD, where 63 allow 8.
+    const int m = tid & 15;
+#pragma unroll 1
+    for (int r = 0; r < HP_CHUNK / 16; ++r) {
+      const int i = 16 * r + (tid >> 4);
+      float* S = s_acc + i * NA;
+      float x = m < NA ? S[m] : 0.f;
+      if (m >= 4 && m <= 6) x *= m == 5 ? -1.f : -0.5f;  // constant factors of the conic's values
+      if (m == 7) x = flush_omega(S, cur + 4 * i);
       __builtin_amdgcn_wave_barrier();
-      if (x0 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m0 * P + g], x0);
-      if (x1 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m1 * P + g], x1);
-      if (x2 != 0.f) unsafeAtomicAdd(&acc[(int64_t)m2 * P + g], x2);
-      for (int m = qs; m < NA; m += 4) S[m] = 0.f;
+      const int64_t g = s_gid[(ctop - ch) & 1][i];
+      if (x != 0.f) unsafeAtomicAdd(&acc[PACKED ? g * HP_NACC + m : m * P + g], x);
+      if (m < NA) S[m] = 0.f;
     }
     __syncthreads();  // totals sent and cleared before the next chunk adds to them
   }
@@ -766,11 +758,37 @@ extern "C" hp_status hp_render_queue_status(const void* queue, int32_t n_req, in
 
 // the backward of stage 1 lives with the forward in k_preprocess.hip
 hp_status hp_preprocess_bwd_launch(const hp_gaussians* g, const hp_view* view, const hp_params* prm, const float* acc,
-                                   hp_gaussians_grad* grad, hipStream_t s);
+                                   bool packed, hp_gaussians_grad* grad, hipStream_t s);
 
 __global__ void k_zero_f32(float* p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.f;
+}
+
+// hp_render_bwd_pixels into accumulators of either layout (k_render_bwd)
+template <bool PACKED>
+static hp_status bwd_pixels(const void* projected, int64_t P, const uint32_t* vals,
+                            const uint32_t* tile_ranges, int32_t n_tiles, const hp_view* view, const hp_params* prm,
+                            const void* mask, int64_t n_active, const float* T, const int32_t* n_contrib,
+                            const float* dL_drgb, const float* dL_dT, const float* dL_dinv_depth, float* acc,
+                            void* stream) {
+  HP_TRY(hp_check_view(view, prm));
+  if (P < 0 || !projected || !mask || n_tiles < 0 || n_active < 0) return HP_ERR_INVALID_ARG;
+  if (P > 0 && !acc) return HP_ERR_INVALID_ARG;
+  if (n_active > 0 && n_tiles > 0 && (!T || !n_contrib || !dL_drgb || !tile_ranges || !vals)) return HP_ERR_INVALID_ARG;
+  const HpGeom g = hp_geom(view->order, prm->tile_log2);
+  if (n_tiles > g.ntile || n_active > g.npix) return HP_ERR_INVALID_ARG;
+  if (P == 0 || n_tiles == 0 || n_active == 0) return HP_OK;
+  RenderArgs A = make_args(g, hp_mask_view((const char*)mask, g), hp_proj_view((const char*)projected, P), vals,
+                           tile_ranges, prm, n_active);
+  if (dL_dinv_depth)
+    hipLaunchKernelGGL((k_render_bwd<true, PACKED>), dim3((unsigned)n_tiles), dim3(256), 0, (hipStream_t)stream, A, P, T,
+                       n_contrib, dL_drgb, dL_dT, dL_dinv_depth, acc);
+  else
+    hipLaunchKernelGGL((k_render_bwd<false, PACKED>), dim3((unsigned)n_tiles), dim3(256), 0, (hipStream_t)stream, A, P, T,
+                       n_contrib, dL_drgb, dL_dT, (const float*)nullptr, acc);
+  HP_CHECK_LAUNCH();
+  return HP_OK;
 }
 
 extern "C" size_t hp_render_bwd_workspace_bytes(int64_t P) { return P < 0 ? 0 : hp_align256((size_t)P * HP_NACC * 4); }
@@ -792,7 +810,7 @@ extern "C" hp_status hp_render_bwd(const hp_gaussians* gs, const void* projected
                            dL_drgb, dL_dT, dL_dinv_depth, grad, (float*)ws, stream);
 }
 
-// hp_render_bwd after its argument checks, with the accumulators [HP_NACC][P]
+// hp_render_bwd after its argument checks, with the accumulators [P][HP_NACC]
 // at `acc` (zeroed here by a kernel)
 hp_status hp_render_bwd_acc(const hp_gaussians* gs, const void* projected, const uint32_t* vals,
                             const uint32_t* tile_ranges, int32_t n_tiles, const hp_view* view, const hp_params* prm,
@@ -805,33 +823,19 @@ hp_status hp_render_bwd_acc(const hp_gaussians* gs, const void* projected, const
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(k_zero_f32, dim3(hp_blocks(gs->P * HP_NACC, 256)), dim3(256), 0, s, acc, gs->P * HP_NACC);
   HP_CHECK_LAUNCH();
-  HP_TRY(hp_render_bwd_pixels(projected, gs->P, vals, tile_ranges, n_tiles, view, prm, mask, n_active, T, n_contrib,
-                              dL_drgb, dL_dT, dL_dinv_depth, acc, stream));
-  return hp_preprocess_bwd_launch(gs, view, prm, acc, grad, s);
+  HP_TRY(bwd_pixels<true>(projected, gs->P, vals, tile_ranges, n_tiles, view, prm, mask, n_active, T, n_contrib,
+                          dL_drgb, dL_dT, dL_dinv_depth, acc, stream));
+  return hp_preprocess_bwd_launch(gs, view, prm, acc, true, grad, s);
 }
+
 
 extern "C" hp_status hp_render_bwd_pixels(const void* projected, int64_t P, const uint32_t* vals,
                                           const uint32_t* tile_ranges, int32_t n_tiles, const hp_view* view,
                                           const hp_params* prm, const void* mask, int64_t n_active, const float* T,
                                           const int32_t* n_contrib, const float* dL_drgb, const float* dL_dT,
                                           const float* dL_dinv_depth, float* acc, void* stream) {
-  HP_TRY(hp_check_view(view, prm));
-  if (P < 0 || !projected || !mask || n_tiles < 0 || n_active < 0) return HP_ERR_INVALID_ARG;
-  if (P > 0 && !acc) return HP_ERR_INVALID_ARG;
-  if (n_active > 0 && n_tiles > 0 && (!T || !n_contrib || !dL_drgb || !tile_ranges || !vals)) return HP_ERR_INVALID_ARG;
-  const HpGeom g = hp_geom(view->order, prm->tile_log2);
-  if (n_tiles > g.ntile || n_active > g.npix) return HP_ERR_INVALID_ARG;
-  if (P == 0 || n_tiles == 0 || n_active == 0) return HP_OK;
-  RenderArgs A = make_args(g, hp_mask_view((const char*)mask, g), hp_proj_view((const char*)projected, P), vals,
-                           tile_ranges, prm, n_active);
-  if (dL_dinv_depth)
-    hipLaunchKernelGGL(k_render_bwd<true>, dim3((unsigned)n_tiles), dim3(256), 0, (hipStream_t)stream, A, P, T,
-                       n_contrib, dL_drgb, dL_dT, dL_dinv_depth, acc);
-  else
-    hipLaunchKernelGGL(k_render_bwd<false>, dim3((unsigned)n_tiles), dim3(256), 0, (hipStream_t)stream, A, P, T,
-                       n_contrib, dL_drgb, dL_dT, (const float*)nullptr, acc);
-  HP_CHECK_LAUNCH();
-  return HP_OK;
+  return bwd_pixels<false>(projected, P, vals, tile_ranges, n_tiles, view, prm, mask, n_active, T, n_contrib, dL_drgb,
+                           dL_dT, dL_dinv_depth, acc, stream);
 }
 
 extern "C" hp_status hp_preprocess_bwd(const hp_gaussians* gs, const hp_view* view, const hp_params* prm,
@@ -841,7 +845,7 @@ extern "C" hp_status hp_preprocess_bwd(const hp_gaussians* gs, const hp_view* vi
   if (!grad) return HP_ERR_INVALID_ARG;
   if (gs->P == 0) return HP_OK;
   if (!acc || !grad->mean || !grad->scale || !grad->rot || !grad->opacity || !grad->sh) return HP_ERR_INVALID_ARG;
-  return hp_preprocess_bwd_launch(gs, view, prm, acc, grad, (hipStream_t)stream);
+  return hp_preprocess_bwd_launch(gs, view, prm, acc, false, grad, (hipStream_t)stream);
 }
 
 // ---- radian-space statistics for adaptive density control -------------------
