@@ -391,7 +391,7 @@ __device__ __forceinline__ int64_t walk_first(uint32_t h) {
 // that walked them alone held up its wave: 250K Gaussians seen by a 75-degree
 // pinhole at Nside 1024 took 105 us to count and 219 us to place, one lane's
 // chain of dependent tests; the shared stack makes that 38 and 11 us (1M
-// Gaussians on the full sphere at Nside 512: 72 + 122 us became 77 + 30 us).
+// Gaussians on the full sphere at Nside 512: 72 + 122 us became 77 + 21 us).
 // Four lanes to a parent read its four children's caps as one 64-byte line.
 // The same nodes pass as in coarse_nodes: the faces, which that walk does not
 // test, are tested with a margin (a face's cap contains its descendants'), so
@@ -697,8 +697,11 @@ __global__ __launch_bounds__(256) void k_hist_rows(const uint32_t* __restrict__ 
 
 // Every staged run to its nodes' places in the task list (the blocks of
 // k_task_walk, in the same order); also the node of every chunk of 64 tasks,
-// nodes strided over the workgroups.  Bound by HBM: 6 B read and 4 B written
-// per task.
+// nodes strided over the workgroups.  6 B read and 4 B written per task, bound
+// by the chain of loads before a run's writes: a task's node and Gaussian are
+// read once and together (31 -> 21 us for 4.8M tasks of 1M Gaussians on the full
+// sphere at Nside 512; with a pass for the nodes' places before one that read
+// the tasks again it waited for memory once more).
 constexpr int kPlaceThreads = 512, kPlaceIlp = 4;
 __global__ __launch_bounds__(kPlaceThreads) void k_task_place(const uint64_t* __restrict__ n_live, int nn, int64_t G,
                                                               TaskStage st, const uint32_t* __restrict__ hoff,
@@ -724,34 +727,28 @@ __global__ __launch_bounds__(kPlaceThreads) void k_task_place(const uint64_t* __
     auto node = [&](uint32_t t) { return (uint32_t)(t < fixed ? st.n[vb * fixed + t] : st.on[ob + (t - fixed)]); };
     __syncthreads();  // the previous run's reads are done
     // kPlaceIlp tasks of a thread at a time, their loads all in flight: the
-    // runs of the widest Gaussians are tens of times the others' length
+    // runs of the widest Gaussians are tens of times the others' length.  A
+    // node's first place is set in the step that holds its first task, so later
+    // steps, whose nodes are others, need no barrier before they set theirs.
     constexpr uint32_t kStep = kPlaceThreads * kPlaceIlp;
-    for (uint32_t t0 = threadIdx.x; t0 < tmax; t0 += kStep) {
-      uint32_t n[kPlaceIlp], before[kPlaceIlp];
+    for (uint32_t b0 = 0; b0 < tmax; b0 += kStep) {
+      uint32_t n[kPlaceIlp], before[kPlaceIlp], g[kPlaceIlp];
 #pragma unroll
       for (int j = 0; j < kPlaceIlp; ++j) {
-        const uint32_t t = t0 + j * kPlaceThreads;
+        const uint32_t t = b0 + threadIdx.x + j * kPlaceThreads;
         n[j] = t < tmax ? node(t) : 0u;
         before[j] = t > 0 && t < tmax ? node(t - 1) : ~0u;
-      }
-#pragma unroll
-      for (int j = 0; j < kPlaceIlp; ++j) {
-        const uint32_t t = t0 + j * kPlaceThreads;
-        if (t < tmax && n[j] != before[j]) s_first[n[j]] = node_off[n0 + n[j]] + hoff[(int64_t)(n0 + n[j]) * G + b] - t;
-      }
-    }
-    __syncthreads();
-    for (uint32_t t0 = threadIdx.x; t0 < tmax; t0 += kStep) {
-      uint32_t n[kPlaceIlp], g[kPlaceIlp];
-#pragma unroll
-      for (int j = 0; j < kPlaceIlp; ++j) {
-        const uint32_t t = t0 + j * kPlaceThreads;
-        n[j] = t < tmax ? node(t) : 0u;
         g[j] = t >= tmax ? 0u : (t < fixed ? st.g[vb * fixed + t] : st.og[ob + (t - fixed)]);
       }
 #pragma unroll
       for (int j = 0; j < kPlaceIlp; ++j) {
-        const uint32_t t = t0 + j * kPlaceThreads;
+        const uint32_t t = b0 + threadIdx.x + j * kPlaceThreads;
+        if (t < tmax && n[j] != before[j]) s_first[n[j]] = node_off[n0 + n[j]] + hoff[(int64_t)(n0 + n[j]) * G + b] - t;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kPlaceIlp; ++j) {
+        const uint32_t t = b0 + threadIdx.x + j * kPlaceThreads;
         const uint64_t pos = t < tmax ? s_first[n[j]] + t : (uint64_t)cap_t;
         if (pos < (uint64_t)cap_t) task_g[pos] = g[j];
       }
