@@ -1302,16 +1302,26 @@ __global__ __launch_bounds__(256) void k_depth_hist(const uint32_t* depth, const
   }
   int64_t t0, t1;
   hpsort::block_tiles(P, &t0, &t1, hpsort::kRadixTile);
-  const int64_t lo = t0 * hpsort::kRadixTile, hi = t1 * hpsort::kRadixTile < P ? t1 * hpsort::kRadixTile : P;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
-    uint32_t k = depth[i];
-    if (CONE) {
-      const float4 d = disc[i];
-      const float cg = sqrtf(fmaxf(0.f, 1.f - d.w * d.w));
-      if (!hp_cap_test(0.f, 0.f, 1.f, sr, cr, d.x, d.y, d.z, d.w, cg)) k = kNoDepth;
-      keys[i] = k;
+  constexpr int kPer = hpsort::kRadixTile / 256;
+  for (int64_t t = t0; t < t1; ++t) {
+    uint32_t key[kPer];
+    float4 d[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int64_t i = t * hpsort::kRadixTile + r * 256 + threadIdx.x;
+      key[r] = i < P ? depth[i] : kNoDepth;
+      if (CONE) d[r] = i < P ? disc[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if (k < kNoDepth) atomicAdd(&s_h[k & 255u], 1u);
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      if (CONE) {
+        const int64_t i = t * hpsort::kRadixTile + r * 256 + threadIdx.x;
+        const float cg = sqrtf(fmaxf(0.f, 1.f - d[r].w * d[r].w));
+        if (!hp_cap_test(0.f, 0.f, 1.f, sr, cr, d[r].x, d[r].y, d[r].z, d[r].w, cg)) key[r] = kNoDepth;
+        if (i < P) keys[i] = key[r];
+      }
+      if (key[r] < kNoDepth) atomicAdd(&s_h[key[r] & 255u], 1u);
+    }
   }
   __syncthreads();
   hist[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = s_h[threadIdx.x];
