@@ -265,15 +265,6 @@ __device__ __forceinline__ int hp_lane() { return (int)__lane_id(); }
 // constant address space lets the compiler use scalar loads into SGPRs.
 typedef const __attribute__((address_space(4))) float* hp_cfloatp;
 typedef const __attribute__((address_space(4))) uint32_t* hp_cu32p;
-// the 64-byte record of Gaussian g (see HpProjView) as four float4
-__device__ __forceinline__ void hp_load_rec(hp_cfloatp rec, uint32_t g, float4& r0, float4& r1, float4& r2,
-                                            float4& r3) {
-  const hp_cfloatp p = rec + 16 * (int64_t)g;
-  r0 = make_float4(p[0], p[1], p[2], p[3]);
-  r1 = make_float4(p[4], p[5], p[6], p[7]);
-  r2 = make_float4(p[8], p[9], p[10], p[11]);
-  r3 = make_float4(p[12], p[13], p[14], p[15]);
-}
 __device__ __forceinline__ uint32_t hp_uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Workgroups go to the 8 XCDs round-robin by index.  Giving each XCD a
@@ -405,17 +396,4 @@ __device__ __forceinline__ float hp_wave_max_dpp(float z) {
   z = fmaxf(z, hp_dpp<0xB1>(z));
   z = fmaxf(z, hp_dpp<0x4E>(z));
   return fmaxf(z, hp_dpp<0x141>(z));
-}
-
-__device__ __forceinline__ uint32_t hp_wave_prefix_u32(uint32_t v, uint32_t* total) {
-  // inclusive scan across the wave, returns exclusive; total in *total
-  uint32_t x = v;
-  const int lane = hp_lane();
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  *total = __shfl(x, 63, 64);
-  return x - v;
 }
