@@ -90,7 +90,7 @@ hp_status hp_bin_sorted_widened(int32_t phase, const void* projected, int64_t P,
 // phase does not read.
 void* hp_bin_spare(void* ws, int64_t P);
 
-// hp_render_bwd after its argument checks, accumulators [HP_NACC][P] at acc
+// hp_render_bwd after its argument checks, accumulators [P][HP_NACC] at acc
 hp_status hp_render_bwd_acc(const hp_gaussians* gs, const void* projected, const uint32_t* vals,
                             const uint32_t* tile_ranges, int32_t n_tiles, const hp_view* view, const hp_params* prm,
                             const void* mask, int64_t n_active, const float* T, const int32_t* n_contrib,

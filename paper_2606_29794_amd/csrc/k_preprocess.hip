@@ -200,27 +200,28 @@ extern "C" hp_status hp_preprocess_batch(const hp_gaussians* g, int32_t n_views,
 // ---------------------------------------------------------------------------
 // Backward of stage 1 (Sec. 3.2, Eqs. backward_lat_scale and grad_via_J_S).
 // Inputs per Gaussian: dL/d(colour, opacity, conic A B C, omega, phi) from the
-// pixel pass.  Sigma_arc = V V^T with V = (1/r) E W R diag(s) and E the unit
+// pixel pass, value-major, or PACKED, the ten values of a Gaussian side by side,
+// with sums that give dL/dSigma_arc without the conic (k_render_bwd).  Sigma_arc = V V^T with V = (1/r) E W R diag(s) and E the unit
 // tangent frame, which equals S_phi J W R diag(s): the latitude term of Eq.
 // backward_lat_scale and the J term of Eq. grad_via_J_S both arrive through
 // the dependence of E and r on the camera-space centre t.
 // ---------------------------------------------------------------------------
-template <int DEG>
+template <int DEG, bool PACKED>
 __global__ __launch_bounds__(256) void k_preprocess_bwd(int64_t P, const float* __restrict__ mean,
                                                         const float* __restrict__ scale, const float* __restrict__ rot,
                                                         const float* __restrict__ sh, HpViewK V, float r_min,
-                                                        float sh_off, const float* __restrict__ acc, bool packed,
+                                                        float sh_off, const float* __restrict__ acc,
                                                         float* __restrict__ gmean, float* __restrict__ gscale,
                                                         float* __restrict__ grot, float* __restrict__ gopac,
                                                         float* __restrict__ gsh) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P) return;
-  // [0..8] as the pixel pass writes them, [9] dL/d(1/r) of the depth channel
+  // as the pixel pass writes them
   float gy[10];
   bool any = false;
 #pragma unroll
   for (int m = 0; m < 10; ++m) {
-    gy[m] = packed ? acc[10 * i + m] : acc[m * P + i];
+    gy[m] = PACKED ? acc[10 * i + m] : acc[m * P + i];
     any = any || gy[m] != 0.f;
   }
   if (!any) return;
@@ -262,13 +263,24 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(int64_t P, const float* 
               c2 = Vm[0][0] * Vm[1][1] - Vm[0][1] * Vm[1][0];
   const float det = c0 * c0 + c1 * c1 + c2 * c2;
   if (!(det > 0.f)) return;
-  const float idet = 1.f / det;
-  const float QA = sc * idet, QB = -sb * idet, QC = sa * idet;
-  // conic -> Sigma_arc:  G_S = -Q G_Q Q with G_Q = [[gA, gB/2], [gB/2, gC]]
-  const float gA = gy[4], gB = 0.5f * gy[5], gC = gy[6];
-  const float t00 = QA * gA + QB * gB, t01 = QA * gB + QB * gC;
-  const float t10 = QB * gA + QC * gB, t11 = QB * gB + QC * gC;
-  const float G00 = -(t00 * QA + t01 * QB), G01 = -(t00 * QB + t01 * QC), G11 = -(t10 * QB + t11 * QC);
+  float G00, G01, G11;  // dL/dSigma_arc
+  if (PACKED) {
+    G00 = 0.5f * gy[4];
+    G01 = 0.5f * gy[5];
+    G11 = 0.5f * gy[6];
+    // dL/domega = cos(phi) [7] - sin(phi) sum m k2 (u1 b - u2 a), (a, b) = Sigma u
+    gy[7] = cp * gy[7] - sp * ((sc - sa) * gy[5] + sb * (gy[4] - gy[6]));
+  } else {
+    const float idet = 1.f / det;
+    const float QA = sc * idet, QB = -sb * idet, QC = sa * idet;
+    // conic -> Sigma_arc:  G_S = -Q G_Q Q with G_Q = [[gA, gB/2], [gB/2, gC]]
+    const float gA = gy[4], gB = 0.5f * gy[5], gC = gy[6];
+    const float t00 = QA * gA + QB * gB, t01 = QA * gB + QB * gC;
+    const float t10 = QB * gA + QC * gB, t11 = QB * gB + QC * gC;
+    G00 = -(t00 * QA + t01 * QB);
+    G01 = -(t00 * QB + t01 * QC);
+    G11 = -(t10 * QB + t11 * QC);
+  }
   // Sigma = V V^T  ->  dL/dV = 2 G V
   float gV[2][3];
 #pragma unroll
@@ -385,9 +397,13 @@ hp_status hp_preprocess_bwd_launch(const hp_gaussians* g, const hp_view* view, c
                                    bool packed, hp_gaussians_grad* grad, hipStream_t s) {
   const dim3 grid(hp_blocks(g->P, 256)), block(256);
   const HpViewK vk = hp_viewk(view);
-#define HP_PRE_BWD(D)                                                                                                \
-  hipLaunchKernelGGL(k_preprocess_bwd<D>, grid, block, 0, s, g->P, g->mean, g->scale, g->rot, g->sh, vk, prm->r_min, \
-                     prm->sh_offset, acc, packed, grad->mean, grad->scale, grad->rot, grad->opacity, grad->sh)
+#define HP_PRE_BWD(D)                                                                                               \
+  if (packed)                                                                                                       \
+    hipLaunchKernelGGL((k_preprocess_bwd<D, true>), grid, block, 0, s, g->P, g->mean, g->scale, g->rot, g->sh, vk,  \
+                       prm->r_min, prm->sh_offset, acc, grad->mean, grad->scale, grad->rot, grad->opacity, grad->sh); \
+  else                                                                                                              \
+    hipLaunchKernelGGL((k_preprocess_bwd<D, false>), grid, block, 0, s, g->P, g->mean, g->scale, g->rot, g->sh, vk, \
+                       prm->r_min, prm->sh_offset, acc, grad->mean, grad->scale, grad->rot, grad->opacity, grad->sh)
   switch (g->sh_degree) {
     case 0: HP_PRE_BWD(0); break;
     case 1: HP_PRE_BWD(1); break;

@@ -285,8 +285,11 @@ __global__ __launch_bounds__(256) void k_render_fwd_batch(RenderBatch B) {
 // Per-Gaussian gradient accumulators written by the pixel pass:
 // [0..2] colour, [3] opacity, [4..6] conic (A, B, C), [7] omega, [8] phi,
 // [9] inverse radial depth 1/r (written only with a depth gradient).
+// The packed ones (k_render_bwd) hold in [4..6] sum m k2 (u1^2, u1 u2, u2^2),
+// twice dL/dSigma, and in [7] dL/domega without its sin(phi) part and cos(phi)
+// factor; the preprocess backward finishes them.
 #define HP_NACC 10
-// dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa - hc a)
+// The value-major ones: dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa - hc a)
 // from an entry's totals S and its record; the first sum is (A - C) S5 + B (S6 - S4)
 __device__ __forceinline__ float flush_omega(const float* S, const float4* rec) {
   const float4 r2 = rec[2];
@@ -301,8 +304,8 @@ struct HpBool {
 // matrix and memory pipes idle while each (wave, entry) visit issues about 90 vector
 // instructions, a quarter of them for the sums over the wave.  What a visit
 // can leave to the Gaussian is left to the flush, which runs once per (block,
-// entry): constant factors and the sin(phi) part of dL/domega, which is a
-// combination of the conic's totals; lanes without a hit take part with alpha =
+// entry), or to the preprocess backward: constant factors and the sin(phi)
+// part of dL/domega, which is a combination of the totals 4..6; lanes without a hit take part with alpha =
 // 0, which needs no further selects.  With these and hp_wave_totals9: 862 ->
 // 773 us (full sphere of order 9, 1 M Gaussians), 314 -> 282 us (pinhole of 75
 // degrees with depth, order 10).
@@ -316,6 +319,13 @@ struct HpBool {
 // (hp_xcd_group_tile): 142 -> 123 us and 766 -> 708 us per view.  Otherwise
 // [10][P], the layout that hp_render_bwd_pixels promises, with contiguous tiles
 // (pinhole with depth: 276 -> 271 us by the flush's fewer registers).
+// The packed ones also take the products of u = Q (a, b) where dL/dconic has
+// those of (a, b): dL/dSigma = -Q dL/dQ Q cancels like the square of a
+// footprint's aspect ratio in what the sums' order and last bits are, and u
+// u^T sums to it directly, at the same instruction count.  Against 64 bits, over
+// 300 steps of 1 M Gaussians on four full spheres of order 9, the worst element
+// of a step's scale gradient went from 2.2e-4 to 3.7e-5 and of its rotation
+// gradient from 4.5e-4 to 2.3e-4 (means over the steps).
 template <bool DEPTH, bool PACKED>
 __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, const float* __restrict__ Tfin,
                                                     const int32_t* __restrict__ ncon, const float* __restrict__ gC,
@@ -458,13 +468,16 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
         Tcur = Tb;
         v[3] = dLda * G;
         // m = -2 dL/dq; values 4..8 leave out their constant factors, which
-        // the flush applies once per Gaussian
+        // the flush or the preprocess backward applies
         const float m = alpha * dLda;
         const float mk = m * k2h;
-        const float ma = mk * a, mb = mk * b;
-        v[4] = ma * a;  // dL/dA = -v4 / 2
-        v[5] = ma * b;  // dL/dB = -v5
-        v[6] = mb * b;  // dL/dC = -v6 / 2
+        // PACKED: of (u1, u2) = Q (a, b), dL/dSigma = 1/2 [[v4, v5], [v5, v6]];
+        // else of (a, b), dL/dA = -v4 / 2, dL/dB = -v5, dL/dC = -v6 / 2
+        const float da = PACKED ? o.u1 : a, db = PACKED ? o.u2 : b;
+        const float ma = mk * da, mb = mk * db;
+        v[4] = ma * da;
+        v[5] = ma * db;
+        v[6] = mb * db;
         // dq/da = 2 fa, dq/db = 2 fb, dq/dc = 2 hc, with k2 = k2(s2, c)
         const float e = qt * d1;
         const float fa = k2h * o.u1 + e * a;
@@ -472,8 +485,8 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
         // motion of (a, b, c) with the Gaussian's longitude / latitude:
         // da/dw = -cos(phi) c + sin(phi) b, db/dw = -sin(phi) a, dc/dw = cos(phi) a
         // da/dp = 0, db/dp = -c, dc/dp = b
-        // Here only the part of c and hc; the part of sin(phi) is the entry's
-        // combination of values 4..6 (flush)
+        // Here only the part of c and hc; the part of sin(phi) is a
+        // combination of the totals 4..6 (flush_omega, k_preprocess_bwd)
         const float mc = m * c;
         if constexpr (FAR) {
           const float mh = m * (0.5f * qt * d2);
@@ -509,8 +522,10 @@ __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, con
       const int i = 16 * r + (tid >> 4);
       float* S = s_acc + i * NA;
       float x = m < NA ? S[m] : 0.f;
-      if (m >= 4 && m <= 6) x *= m == 5 ? -1.f : -0.5f;  // constant factors of the conic's values
-      if (m == 7) x = flush_omega(S, cur + 4 * i);
+      if constexpr (!PACKED) {
+        if (m >= 4 && m <= 6) x *= m == 5 ? -1.f : -0.5f;  // constant factors of the conic's values
+        if (m == 7) x = flush_omega(S, cur + 4 * i);
+      }
       __builtin_amdgcn_wave_barrier();
       const int64_t g = s_gid[(ctop - ch) & 1][i];
       if (x != 0.f) unsafeAtomicAdd(&acc[PACKED ? g * HP_NACC + m : m * P + g], x);

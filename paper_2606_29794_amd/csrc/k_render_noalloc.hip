@@ -6,7 +6,7 @@
 
 #include "hp_common.h"
 
-// accumulators of the pixel pass: [10][P] floats for P <= HP_NOALLOC_MAX_P
+// accumulators of the pixel pass: [P][10] floats for P <= HP_NOALLOC_MAX_P
 // (40 MiB, held on every device the library runs on until the process ends)
 static __device__ __align__(256) float scratch[10 * (size_t)HP_NOALLOC_MAX_P];
 
