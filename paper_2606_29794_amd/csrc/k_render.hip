@@ -290,8 +290,11 @@ __global__ __launch_bounds__(256) void k_render_fwd_batch(RenderBatch B) {
 // factor; the preprocess backward finishes them.
 #define HP_NACC 10
 // The value-major ones: dL/domega = -v7 with v7 = sin(phi) sum m (fa b - fb a) - cos(phi) sum m (c fa - hc a)
-// from an entry's totals S and its record; the first sum is (A - C) S5 + B (S6 - S4)
+// from an entry's totals S and its record; the first sum is (A - C) S5 + B (S6 - S4).
+// An entry that no pixel hit has no totals, and its conic may not be finite
+// (1 / det of a footprint far below a pixel): nothing is made of it.
 __device__ __forceinline__ float flush_omega(const float* S, const float4* rec) {
+  if (S[4] == 0.f && S[5] == 0.f && S[6] == 0.f && S[7] == 0.f) return 0.f;
   const float4 r2 = rec[2];
   return rec[1].w * S[7] - rec[0].y * ((r2.y - r2.w) * S[5] + r2.z * (S[6] - S[4]));
 }
