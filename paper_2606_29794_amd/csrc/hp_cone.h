@@ -21,6 +21,10 @@
 struct HpCone {
   float sr, cr;
 };
+// Word behind the two in a mask that holds its cone.  A mask buffer written
+// before masks had one (kept in a file, or by another build) has other bytes
+// there, and its Gaussians are all kept.
+constexpr uint32_t kConeMark = 0x656e6f43u;
 static inline HpCone hp_view_cone(const hp_view* v, int kt) {
   double a = M_PI;
   if (v->cam_type == HP_CAM_FISHEYE) {

@@ -54,7 +54,7 @@ HP_HD HpGridView hp_grid_view(void* base, const HpGeom& g) {
 struct HpMaskView {
   int64_t* n_active;
   int32_t* n_tiles;
-  float* cone;            // (sin, cos) of half the bounding cone's angle (hp_cone.h)
+  float* cone;            // (sin, cos) of half the bounding cone's angle, then kConeMark (hp_cone.h)
   int32_t* tile_start;    // [ntile] first compact pixel slot of the tile
   int32_t* tile_count;    // [ntile] active pixels in the tile
   int32_t* tile_compact;  // [ntile] compact active tile id or -1

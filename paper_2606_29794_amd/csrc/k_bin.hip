@@ -5,6 +5,7 @@
 // without a stack, pruning subtrees whose cap misses the disc or that hold no
 // active pixel.  Gaussians are processed in order of radial depth so that the
 // pair list is depth-ordered, which the stable tile sort then preserves.
+#include "hp_cone.h"
 #include "hp_sort_impl.h"
 #include <type_traits>
 
@@ -1282,6 +1283,15 @@ static unsigned fine_grid(int64_t nt) {
 // Also marks the count unfinished (see depth_order) and empties the walk's
 // overflow part.
 constexpr uint32_t kNoDepth = 0x7f800000u;  // +inf
+// (sin, cos) of half the mask's cone, widened; (1, 0), which every disc
+// passes, for a mask without one
+__device__ __forceinline__ void read_cone(const float* __restrict__ cone, float wsin, float wcos, float* sr,
+                                          float* cr) {
+  if (__float_as_uint(cone[2]) != kConeMark) return;
+  *sr = cone[0];
+  *cr = cone[1];
+  widen_half(wsin, wcos, sr, cr);
+}
 template <bool CONE>
 __global__ __launch_bounds__(256) void k_depth_hist(const uint32_t* depth, const float4* __restrict__ disc, int64_t P,
                                                     const float* __restrict__ cone, float wsin, float wcos,
@@ -1295,11 +1305,7 @@ __global__ __launch_bounds__(256) void k_depth_hist(const uint32_t* depth, const
   s_h[threadIdx.x] = 0u;
   __syncthreads();
   float sr = 1.f, cr = 0.f;
-  if (CONE) {
-    sr = cone[0];
-    cr = cone[1];
-    widen_half(wsin, wcos, &sr, &cr);
-  }
+  if (CONE) read_cone(cone, wsin, wcos, &sr, &cr);
   int64_t t0, t1;
   hpsort::block_tiles(P, &t0, &t1, hpsort::kRadixTile);
   constexpr int kPer = hpsort::kRadixTile / 256;
@@ -1358,11 +1364,7 @@ __global__ __launch_bounds__(1024) void k_depth_sort_small(const uint32_t* __res
     s_live = 0u;
   }
   float sr = 1.f, cr = 0.f;
-  if (CONE) {
-    sr = cone[0];
-    cr = cone[1];
-    widen_half(wsin, wcos, &sr, &cr);
-  }
+  if (CONE) read_cone(cone, wsin, wcos, &sr, &cr);
   __syncthreads();
   uint32_t key[kSmallIpt], id[kSmallIpt];
 #pragma unroll

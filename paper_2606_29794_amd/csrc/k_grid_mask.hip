@@ -217,6 +217,7 @@ __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t
     *n_tiles = til;
     cone[0] = cone_val.sr;
     cone[1] = cone_val.cr;
+    cone[2] = __uint_as_float(kConeMark);
   }
 }
 
