@@ -18,8 +18,8 @@
 // Candidates are the pairs of hp_bin_sorted with every test angle widened by a
 // margin that contains both sets (one ring step for RING, plus the distance
 // from a query point to the nearest pixel centre of its tile); they arrive in
-// per-tile depth order, and one block per tile keeps the entries that pass,
-// compacting the tile's list in place, so the order is preserved.
+// per-tile depth order, and one wave or workgroup per tile keeps the entries
+// that pass, compacting the tile's list in place, so the order is preserved.
 #include "hp_common.h"
 
 namespace {
@@ -171,12 +171,13 @@ __global__ __launch_bounds__(256) void k_query_gauss(int64_t P, const float4* __
 // in flight together); the four waves of a workgroup take four neighbouring
 // tiles, whose lists hold mostly the same Gaussians in the same order, so
 // that part of the gathers meet in the CU's cache and no barrier orders the
-// waves.  1M Gaussians on the full sphere at Nside 512, RING x 4, 49M
+// waves, or share one tile (SHARED, below).  1M Gaussians on the full sphere at Nside 512, RING x 4, 49M
 // candidates: 619 us with a workgroup per tile and the trigonometry per
 // candidate, 446 us with that done once per Gaussian, 351 us with predicates as
 // wave masks and two lanes to a record.  Bound by the vector instructions of
 // the ring tests (225 us of issue) and by the gathers.
 constexpr int kQueryIlp = 4;
+constexpr int kRingShared = 1024;  // RING: tiles up to which a workgroup takes one
 
 // The 32-byte records of 64 list entries: two lanes fetch a record together,
 // one 16-byte half each (a lane per record spent two cache accesses on it, and
@@ -199,7 +200,14 @@ __device__ __forceinline__ RingGauss pair_load(const float4* __restrict__ gauss,
   return G;
 }
 
-template <int MODE>
+// SHARED: the four waves of a workgroup take one tile's list together, a batch
+// of kQueryIlp x 64 entries each at a time.  A wave each leaves the chip idle
+// where tiles are few, and waits for its gathers alone.  Views of 3M Gaussians
+// with a wave and with a workgroup per tile: RING x 4 and 192 tiles 3617 and
+// 1868 us, 768 tiles 1902 and 1328, 3,072 tiles 1679 and 1726 (RING x 1: 2453 and
+// 2562); NESTED x 4, whose tests are short beside the gathers, 2768 and 1531 us
+// at 192 tiles, 1521 and 1443 at 3,072, 2610 and 2492 at 12,288.
+template <int MODE, bool SHARED>
 __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) {
   if (*A.n_pairs > A.capacity) return;  // the candidates were not written
   __shared__ float4 s_pts[4][MODE == HP_QUERY_NESTED ? kMaxPts : 1];
@@ -207,8 +215,10 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
   __shared__ uint32_t s_keys[4][kMaxRings], s_lens[4][kMaxRings];
   const int lane = hp_lane();
   const int wv = (int)hp_uniform(threadIdx.x >> 6);
-  const int k = 4 * hp_xcd_tile((int)blockIdx.x, (int)gridDim.x) + wv;
-  if (k >= n_tiles) return;  // waves are independent: no barrier below
+  __shared__ uint32_t s_kept[2][4];  // SHARED: entries kept per wave, by step parity
+  const int wg = hp_xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  const int k = SHARED ? wg : 4 * wg + wv;
+  if (k >= n_tiles) return;  // (SHARED: none; else the waves are independent, with no barrier below)
   float4* s_pt = s_pts[wv];
   RingSlot* s_ring = s_rings[wv];
   uint32_t *s_key = s_keys[wv], *s_len = s_lens[wv];
@@ -278,7 +288,10 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
   constexpr uint64_t kEven = 0x5555555555555555ull, kOdd = ~kEven;
   const bool odd = (lane & 1) != 0;
   uint32_t kept = 0;
-  for (uint32_t base = s; base < e; base += kQueryIlp * 64) {
+  constexpr uint32_t kStep = (SHARED ? 4 : 1) * kQueryIlp * 64;
+  int par = 0;
+  for (uint32_t step = s; step < e; step += kStep, par ^= 1) {
+    const uint32_t base = SHARED ? step + (uint32_t)wv * (kQueryIlp * 64) : step;
     // RING: entry lane / 2 for the even lanes, 32 + lane / 2 for the odd ones
     // (pair_load); NESTED: entry `lane`
     uint32_t g[kQueryIlp], ga[kQueryIlp], gb[kQueryIlp];
@@ -328,19 +341,33 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
         if (open == 0) break;
       }
     }
-    // every entry of these has been read (the tests used them), and the next
-    // ones lie behind them: the kept ones move down to the tile's next free
-    // slots, in order
+    // the kept ones of these entries move down to the tile's next free slots, in
+    // order: every one of them has been read (the tests used them; SHARED: the
+    // barrier is behind all four waves' reads), and the next ones lie behind them
+    uint32_t at = s + kept;
+    if constexpr (SHARED) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int q = 0; q < kQueryIlp; ++q) mine += (uint32_t)__popcll(m[q] & have[q]);
+      if (lane == 0) s_kept[par][wv] = mine;
+      __syncthreads();  // (the other set is written in the next step, past every read of it)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        at += w < wv ? s_kept[par][w] : 0u;
+        kept += s_kept[par][w];
+      }
+    }
 #pragma unroll
     for (int q = 0; q < kQueryIlp; ++q) {
       m[q] &= have[q];
       // kept entries before this lane's
       const uint64_t before = MODE == HP_QUERY_RING ? (odd ? kEven | (kOdd & below) : kEven & below) : below;
-      if ((m[q] >> lane) & 1ull) A.vals[s + kept + (uint32_t)__popcll(m[q] & before)] = g[q];
-      kept += (uint32_t)__popcll(m[q]);
+      if ((m[q] >> lane) & 1ull) A.vals[at + (uint32_t)__popcll(m[q] & before)] = g[q];
+      at += (uint32_t)__popcll(m[q]);
     }
+    if (!SHARED) kept = at - s;
   }
-  if (lane == 0) {
+  if (SHARED ? threadIdx.x == 0 : lane == 0) {
     A.ranges[2 * k + 1] = s + kept;
     if (A.n_kept) atomicAdd(A.n_kept, (unsigned long long)kept);
   }
@@ -391,11 +418,13 @@ extern "C" hp_status hp_bin_query(int32_t phase, int32_t mode, int32_t f, const 
   HP_CHECK_LAUNCH();
   QueryArgs A{mode, kq, fl, g.kt, mv.active_tiles, gauss, vals, tile_ranges, n_pairs, capacity,
               (unsigned long long*)n_kept};
-  const dim3 wgs(hp_blocks(n_tiles, 4));
-  if (mode == HP_QUERY_RING)
-    hipLaunchKernelGGL(k_query_filter<HP_QUERY_RING>, wgs, dim3(256), 0, s, A, (int)n_tiles);
+  const dim3 per_tile((unsigned)n_tiles), per_four(hp_blocks(n_tiles, 4));
+  if (mode == HP_QUERY_NESTED)
+    hipLaunchKernelGGL((k_query_filter<HP_QUERY_NESTED, true>), per_tile, dim3(256), 0, s, A, (int)n_tiles);
+  else if (n_tiles <= kRingShared)
+    hipLaunchKernelGGL((k_query_filter<HP_QUERY_RING, true>), per_tile, dim3(256), 0, s, A, (int)n_tiles);
   else
-    hipLaunchKernelGGL(k_query_filter<HP_QUERY_NESTED>, wgs, dim3(256), 0, s, A, (int)n_tiles);
+    hipLaunchKernelGGL((k_query_filter<HP_QUERY_RING, false>), per_four, dim3(256), 0, s, A, (int)n_tiles);
   HP_CHECK_LAUNCH();
   return HP_OK;
 }
