@@ -482,14 +482,22 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 5) void k_ssim_fwd(SsimArgs A, con
           const int cy = py + b, cx = px + a;
           const float m = s.in[0][cy][cx];
           if (m == 0.f) continue;
-          const int cq = ZONES ? cy * H + cx : 0;
-          const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
-          const float w = polar ? m * __expf(-(float)(ss_dist2(up, uq) * A.wscale))
-                                : m * (A.g[a] * A.g[b]);
+          float xs[3], ys[3];  // read before the weight, whose chain is long
+#pragma unroll
+          for (int ch = 0; ch < 3; ++ch) {
+            xs[ch] = s.in[1 + ch][cy][cx];
+            ys[ch] = s.in[4 + ch][cy][cx];
+          }
+          float w = m * (A.g[a] * A.g[b]);
+          if (polar) {
+            const int cq = ZONES ? cy * H + cx : 0;
+            const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
+            w = m * __expf(-(float)(ss_dist2(up, uq) * A.wscale));
+          }
           Sm[0] += w;
 #pragma unroll
           for (int ch = 0; ch < 3; ++ch) {
-            const float x = s.in[1 + ch][cy][cx], y = s.in[4 + ch][cy][cx];
+            const float x = xs[ch], y = ys[ch];
             const float wx = w * x, wy = w * y;
             Sm[1 + ch] += wx;
             Sm[4 + ch] += wy;
@@ -781,13 +789,15 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 6) void k_ssim_bwd(SsimArgs A, con
       const int cp = ZONES ? (py + SS_R) * H + px + SS_R : 0;
       const double up[3] = {s.dir[0][cp], s.dir[1][cp], s.dir[2][cp]};
       for (int b = 0; b < SS_W; ++b) {
-#pragma unroll(ZONES ? 1 : SS_W)
         for (int a = 0; a < SS_W; ++a) {
           const int cy = py + b, cx = px + a, cq = ZONES ? cy * H + cx : 0;
-          const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
           // q's own window at p: the great-circle Gaussian for a polar q,
           // the (symmetric) chart taps otherwise
-          const float w = (ZONES && s.polar[cq]) ? __expf(-(float)(ss_dist2(up, uq) * A.wscale)) : A.g[a] * A.g[b];
+          float w = A.g[a] * A.g[b];
+          if (ZONES && s.polar[cq]) {
+            const double uq[3] = {s.dir[0][cq], s.dir[1][cq], s.dir[2][cq]};
+            w = __expf(-(float)(ss_dist2(up, uq) * A.wscale));
+          }
 #pragma unroll
           for (int k = 0; k < 9; ++k) Sm[k] = fmaf(w, s.in[k][cy][cx], Sm[k]);
         }
