@@ -554,12 +554,66 @@ __global__ __launch_bounds__(256, ZONES ? 3 : 5) void k_ssim_fwd(SsimArgs A, con
                                    s_red[1][0] + s_red[1][1] + s_red[1][2] + s_red[1][3]);
 }
 
+// Sums over the n partials of the tiles.  Bound by how many cache lines one
+// compute unit waits for at a time: a workgroup that reads them all, two partials
+// a load, takes 4.7 us at 12,288 (one a load: 5.7), 13.1 at 49,152 and 48 at
+// 196,608; from kSsReduce on each piece of 1,024 is summed by its own workgroup
+// first (4.6 us, left in 64 bits over the piece's first entries), and
+// k_ssim_reduce takes 4.6 us more.
+constexpr int kSsReduce = 16384, kSsPiece = 1024;
+__global__ __launch_bounds__(256) void k_ssim_pieces(float2* __restrict__ part, int n) {
+  __shared__ double s[2][4];
+  float2* mine = part + kSsPiece * (int64_t)blockIdx.x;
+  const int m = min(n - kSsPiece * (int)blockIdx.x, kSsPiece);
+  float2 p[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int i = (int)threadIdx.x + 256 * j;
+    p[j] = i < m ? mine[i] : make_float2(0.f, 0.f);
+  }
+  double a = 0, b = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { a += p[j].x; b += p[j].y; }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    a += __shfl_xor(a, off, 64);
+    b += __shfl_xor(b, off, 64);
+  }
+  if (hp_lane() == 0) { s[0][threadIdx.x >> 6] = a; s[1][threadIdx.x >> 6] = b; }
+  __syncthreads();  // every read of the piece is done
+  if (threadIdx.x == 0) {
+    double* out = reinterpret_cast<double*>(mine);
+    out[0] = s[0][0] + s[0][1] + s[0][2] + s[0][3];
+    // (a last piece of one entry is not the last of the array, whose length, 12 4^k
+    // of at least 49,152, is a multiple of the piece's)
+    out[1] = s[1][0] + s[1][1] + s[1][2] + s[1][3];
+  }
+}
+
 // single block: mean SSIM, mean L1, loss
+template <bool PIECES>
 __global__ __launch_bounds__(1024) void k_ssim_reduce(const float2* __restrict__ part, int n, int64_t n_active,
                                                       float lam, float* __restrict__ out) {
   __shared__ double s[2][16];
   double a = 0, b = 0;
-  for (int i = threadIdx.x; i < n; i += 1024) { a += part[i].x; b += part[i].y; }
+  if (PIECES) {
+    for (int i = threadIdx.x; i < (n + kSsPiece - 1) / kSsPiece; i += 1024) {
+      const double* p = reinterpret_cast<const double*>(part + kSsPiece * (int64_t)i);
+      a += p[0];
+      b += p[1];
+    }
+  } else {
+    const float4* p2 = reinterpret_cast<const float4*>(part);
+    for (int i = threadIdx.x; i < n / 2; i += 1024) {
+      const float4 p = p2[i];
+      a += (double)p.x + p.z;
+      b += (double)p.y + p.w;
+    }
+    if ((n & 1) != 0 && threadIdx.x == 0) {
+      a += part[n - 1].x;
+      b += part[n - 1].y;
+    }
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     a += __shfl_xor(a, off, 64);
@@ -940,8 +994,15 @@ static hp_status ssim_fwd_launch(const SsimArgs& A, bool zones, const float* img
     default: HP_TRY(ssim_fwd_launch_b<1>(A, zones, img, ref, n_tiles, ssim_map, Gm, part, s)); break;
   }
   // one partial per forward workgroup
-  hipLaunchKernelGGL(k_ssim_reduce, dim3(1), dim3(1024), 0, s, (const float2*)part, n_tiles,
-                     A.n_active, lam, out);
+  if (n_tiles > kSsReduce) {
+    hipLaunchKernelGGL(k_ssim_pieces, dim3(hp_blocks(n_tiles, kSsPiece)), dim3(256), 0, s, part, (int)n_tiles);
+    HP_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_ssim_reduce<true>, dim3(1), dim3(1024), 0, s, (const float2*)part, (int)n_tiles, A.n_active,
+                       lam, out);
+  } else {
+    hipLaunchKernelGGL(k_ssim_reduce<false>, dim3(1), dim3(1024), 0, s, (const float2*)part, (int)n_tiles, A.n_active,
+                       lam, out);
+  }
   HP_CHECK_LAUNCH();
   return HP_OK;
 }
