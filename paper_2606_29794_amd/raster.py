@@ -36,12 +36,19 @@ def _dense(t):
     return t.contiguous()
 
 
+# private functions of torch: a build without them takes the public way
+_raw_handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _raw_stream(device=None) -> int:
     """Handle of the device's current stream, without the Python stream object
     that torch.cuda.current_stream makes: a pass asks 15 times, at 2.5 us each
     for the object and 0.3 us for the handle."""
+    if _raw_handle is None or _raw_device is None:
+        return torch.cuda.current_stream(device).cuda_stream
     index = None if device is None else device.index
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice() if index is None else index)
+    return _raw_handle(_raw_device() if index is None else index)
 
 
 def _stream():
