@@ -334,7 +334,8 @@ def kernel_breakdown(R, params, cams, targets, torch, A):
         "evaluated_pixel_pairs": evals,
         "composited_pixel_pairs": used,
         "roofline": {
-            "bound": "alu", "kernel": "k_render_bwd",
+            # the stand-alone pixel pass; a step's own launches add to packed accumulators
+            "bound": "alu", "kernel": "k_render_bwd", "accumulators": "value-major",
             "achieved": None, "peak": PEAK_VALU_TFLOPS, "unit": "TFLOP/s", "frac": None, "traffic": None,
         },
         "stage_roofline": {

@@ -139,8 +139,9 @@ hp_status hp_grid_init(int32_t order, const hp_params* prm, void* grid, size_t g
  * mask: device buffer of hp_mask_bytes(order, tile_log2) bytes receiving:
  *   the sorted list of active NESTED pixels (int32), per tile the offset of
  *   its first active pixel in that list, its active count and 256-bit
- *   membership, the compact index of every active tile, and per quadtree node
- *   whether any active pixel lies below it.
+ *   membership, the compact index of every active tile, per quadtree node
+ *   whether any active pixel lies below it, and a cone around the optical axis
+ *   that bounds the active tiles.
  * hp_mask_counts waits for `stream` and returns n_active (active pixels) and
  * n_tiles (active tiles); outputs of the other calls are indexed by these.
  * hp_mask_active_pix returns the device pointer to the int32 active pixel

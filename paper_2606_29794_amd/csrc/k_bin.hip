@@ -1,20 +1,23 @@
 // k_bin.hip -- stage 2a of Alg. 1: tile assignment (QueryDisc) and pair
 // emission.  Tile t is assigned to Gaussian i when the angle between t's cap
 // centre and i's direction is at most r_s,i + R_t + guard; the NESTED
-// quadtree of caps (each containing its children's) is walked depth-first
-// without a stack, pruning subtrees whose cap misses the disc or that hold no
-// active pixel.  Gaussians are processed in order of radial depth so that the
-// pair list is depth-ordered, which the stable tile sort then preserves.
+// quadtree of caps (each containing its children's) is walked from the 12
+// faces, pruning subtrees whose cap misses the disc or that hold no active
+// pixel.  Gaussians are processed in order of radial depth so that every list
+// is depth-ordered.
 #include "hp_cone.h"
 #include "hp_sort_impl.h"
 #include <type_traits>
 
 // Work is split in two so that no lane walks a large Gaussian alone:
-//  coarse: each Gaussian walks the quadtree from the 12 faces down to the
-//          split level Ls = kt - 3 and lists the nodes that pass ("tasks");
-//  fine:   one wave per task tests the (at most 64) tiles below its node.
-// Both walks run twice (count, then write at scanned offsets) so that tasks
-// and pairs stay in depth order.
+//  coarse: the Gaussians' nodes at the split level Ls = kt - 3 ("tasks");
+//  fine:   the (at most 64) tiles below a task's node.
+// hp_bin_sorted (k_bin_cols, k_bin_emit_sorted) takes its tasks in node order,
+// depth order inside a node: up to kListNodes nodes straight from one walk
+// whose waves share a stack (k_task_walk, k_task_place), beyond them from a walk
+// per Gaussian and a stable sort by node.  hp_bin writes (tile, Gaussian) pairs
+// in depth order for a stable tile sort: it walks per Gaussian too, and both
+// its stages run twice, to count and to write at scanned offsets.
 constexpr int kSplitDepth = 3;
 
 struct BinWs {

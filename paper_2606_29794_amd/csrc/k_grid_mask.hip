@@ -157,7 +157,6 @@ __global__ __launch_bounds__(256) void k_mask_tiles(int order, int b, int cam, d
 // a run of ntile / 1024 tiles per thread, read and written strided, 196,608
 // tiles (order 11) took 611 us, now 62; 49,152 (order 10) 153, now 16; 768
 // (order 7) 4.4, now 2.1.
-typedef int HpInt4 __attribute__((ext_vector_type(4), aligned(4)));  // the mask is the caller's: 4-byte alignment
 __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t* __restrict__ count,
                                                     int32_t* __restrict__ start, int32_t* __restrict__ compact,
                                                     int32_t* __restrict__ active_tiles, int64_t* n_active,
@@ -166,14 +165,14 @@ __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t
   const int tid = threadIdx.x, lane = hp_lane(), wv = tid >> 6;
   auto fetch = [&](int64_t base) {
     const int64_t i = base + 4 * tid;
-    return i < ntile ? *reinterpret_cast<const HpInt4*>(count + i) : HpInt4{0, 0, 0, 0};
+    return i < ntile ? *reinterpret_cast<const int4*>(count + i) : make_int4(0, 0, 0, 0);
   };
   int64_t pix = 0;  // of the steps before
   int32_t til = 0;
-  HpInt4 c = fetch(0);
+  int4 c = fetch(0);
   int par = 0;
   for (int64_t base = 0; base < ntile; base += 4096, par ^= 1) {
-    const HpInt4 next = fetch(base + 4096);
+    const int4 next = fetch(base + 4096);
     const uint32_t p = (uint32_t)(c.x + c.y + c.z + c.w);
     const uint32_t a = (uint32_t)((c.x > 0) + (c.y > 0) + (c.z > 0) + (c.w > 0));
     const uint32_t pi = hpsort::wave_inclusive<uint32_t>(p), ai = hpsort::wave_inclusive<uint32_t>(a);
@@ -194,9 +193,9 @@ __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t
     const int64_t i = base + 4 * tid;
     if (i < ntile) {
       const int32_t s0 = (int32_t)(pix + pb);
-      *reinterpret_cast<HpInt4*>(start + i) = HpInt4{s0, s0 + c.x, s0 + c.x + c.y, s0 + c.x + c.y + c.z};
+      *reinterpret_cast<int4*>(start + i) = make_int4(s0, s0 + c.x, s0 + c.x + c.y, s0 + c.x + c.y + c.z);
       int32_t t = til + (int32_t)ab;
-      HpInt4 id;
+      int4 id;
       auto place = [&](int32_t n, int32_t k) -> int32_t {
         if (n <= 0) return -1;
         active_tiles[t] = (int32_t)i + k;
@@ -206,7 +205,7 @@ __global__ __launch_bounds__(1024) void k_mask_scan(int64_t ntile, const int32_t
       id.y = place(c.y, 1);
       id.z = place(c.z, 2);
       id.w = place(c.w, 3);
-      *reinterpret_cast<HpInt4*>(compact + i) = id;
+      *reinterpret_cast<int4*>(compact + i) = id;
     }
     pix += pt;
     til += (int32_t)at;

@@ -89,7 +89,7 @@ __device__ __forceinline__ float4 stage_load(const float4* __restrict__ rec, uin
 // directions, (sin, cos) of half the largest angle to them, rounded up.  A
 // list entry whose r_s disc misses this cap has q > 9 at every pixel of the
 // wave (the 3-sigma ellipse lies inside the disc), so the wave skips it.
-// The five floats sit in scalar registers: as vector registers they held the
+// The six floats sit in scalar registers: as vector registers they held the
 // backward at 6 waves per SIMD instead of 7 (fisheye, order 8: 150 -> 142 us;
 // full sphere, order 9: 773 -> 765 us).
 __device__ __forceinline__ float uniform_f32(float v) { return __uint_as_float(hp_uniform(__float_as_uint(v))); }
@@ -778,11 +778,10 @@ extern "C" hp_status hp_render_queue_status(const void* queue, int32_t n_req, in
 hp_status hp_preprocess_bwd_launch(const hp_gaussians* g, const hp_view* view, const hp_params* prm, const float* acc,
                                    bool packed, hp_gaussians_grad* grad, hipStream_t s);
 
-// four floats a thread, in one store where p (a caller's workspace) is aligned for
-// it: 13.1 -> 8.5 us for 40 MB
+// four floats a thread in one store: 13.1 -> 8.5 us for 40 MB
 __global__ void k_zero_f32(float* p, int64_t n) {
   const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
-  if (i + 4 <= n && ((uintptr_t)p & 15u) == 0)
+  if (i + 4 <= n)
     *reinterpret_cast<float4*>(p + i) = make_float4(0.f, 0.f, 0.f, 0.f);
   else
     for (int64_t j = i; j < n && j < i + 4; ++j) p[j] = 0.f;
@@ -850,7 +849,6 @@ hp_status hp_render_bwd_acc(const hp_gaussians* gs, const void* projected, const
                           dL_drgb, dL_dT, dL_dinv_depth, acc, stream));
   return hp_preprocess_bwd_launch(gs, view, prm, acc, true, grad, s);
 }
-
 
 extern "C" hp_status hp_render_bwd_pixels(const void* projected, int64_t P, const uint32_t* vals,
                                           const uint32_t* tile_ranges, int32_t n_tiles, const hp_view* view,
