@@ -328,7 +328,8 @@ struct HpBool {
 // u^T sums to it directly, at the same instruction count.  Against 64 bits, over
 // 300 steps of 1 M Gaussians on four full spheres of order 9, the worst element
 // of a step's scale gradient went from 2.2e-4 to 3.7e-5 and of its rotation
-// gradient from 4.5e-4 to 2.3e-4 (means over the steps).
+// gradient from 4.5e-4 to 2.3e-4 (means over the steps); a launch, whose flush
+// no longer reads the records, from 694 to 674 us.
 template <bool DEPTH, bool PACKED>
 __global__ __launch_bounds__(256) void k_render_bwd(RenderArgs A, int64_t P, const float* __restrict__ Tfin,
                                                     const int32_t* __restrict__ ncon, const float* __restrict__ gC,
