@@ -283,14 +283,17 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
   }
   __builtin_amdgcn_wave_barrier();
 
-  const uint32_t s = hp_uniform(A.ranges[2 * k]), e = hp_uniform(A.ranges[2 * k + 1]);
+  // the tile's list; entries are numbered from its start, so that a list at the end
+  // of 2^32 entries does not wrap
+  const uint32_t s = hp_uniform(A.ranges[2 * k]), n = hp_uniform(A.ranges[2 * k + 1]) - s;
+  uint32_t* list = A.vals + s;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   constexpr uint64_t kEven = 0x5555555555555555ull, kOdd = ~kEven;
   const bool odd = (lane & 1) != 0;
   uint32_t kept = 0;
   constexpr uint32_t kStep = (SHARED ? 4 : 1) * kQueryIlp * 64;
   int par = 0;
-  for (uint32_t step = s; step < e; step += kStep, par ^= 1) {
+  for (uint32_t step = 0; step < n; step += kStep, par ^= 1) {
     const uint32_t base = SHARED ? step + (uint32_t)wv * (kQueryIlp * 64) : step;
     // RING: entry lane / 2 for the even lanes, 32 + lane / 2 for the odd ones
     // (pair_load); NESTED: entry `lane`
@@ -300,14 +303,14 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
     for (int q = 0; q < kQueryIlp; ++q) {
       if (MODE == HP_QUERY_RING) {
         const uint32_t ia = base + 64u * q + (uint32_t)(lane >> 1), ib = ia + 32u;
-        ga[q] = ia < e ? A.vals[ia] : 0u;
-        gb[q] = ib < e ? A.vals[ib] : 0u;
+        ga[q] = ia < n ? list[ia] : 0u;
+        gb[q] = ib < n ? list[ib] : 0u;
         g[q] = odd ? gb[q] : ga[q];
-        have[q] = __builtin_amdgcn_ballot_w64((odd ? ib : ia) < e);
+        have[q] = __builtin_amdgcn_ballot_w64((odd ? ib : ia) < n);
       } else {
         const uint32_t idx = base + 64u * q + (uint32_t)lane;
-        have[q] = __builtin_amdgcn_ballot_w64(idx < e);
-        g[q] = idx < e ? A.vals[idx] : 0u;
+        have[q] = __builtin_amdgcn_ballot_w64(idx < n);
+        g[q] = idx < n ? list[idx] : 0u;
       }
       m[q] = 0;
     }
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
     // the kept ones of these entries move down to the tile's next free slots, in
     // order: every one of them has been read (the tests used them; SHARED: the
     // barrier is behind all four waves' reads), and the next ones lie behind them
-    uint32_t at = s + kept;
+    uint32_t at = kept;
     if constexpr (SHARED) {
       uint32_t mine = 0;
 #pragma unroll
@@ -362,10 +365,10 @@ __global__ __launch_bounds__(256) void k_query_filter(QueryArgs A, int n_tiles) 
       m[q] &= have[q];
       // kept entries before this lane's
       const uint64_t before = MODE == HP_QUERY_RING ? (odd ? kEven | (kOdd & below) : kEven & below) : below;
-      if ((m[q] >> lane) & 1ull) A.vals[at + (uint32_t)__popcll(m[q] & before)] = g[q];
+      if ((m[q] >> lane) & 1ull) list[at + (uint32_t)__popcll(m[q] & before)] = g[q];
       at += (uint32_t)__popcll(m[q]);
     }
-    if (!SHARED) kept = at - s;
+    if (!SHARED) kept = at;
   }
   if (SHARED ? threadIdx.x == 0 : lane == 0) {
     A.ranges[2 * k + 1] = s + kept;
